@@ -122,10 +122,15 @@ void perm_ws_pointers(WaPermLaunch& a, const PermWs& L, char* base) {
   a.slices = L.slices;
 }
 
-// Attention workspace: [scheduler state][V^T copy][row_ptr][col_idx]; the CSR entry point uses the
-// first two parts. The scheduler part is sized for the largest n_xcd.
+// Attention workspace: [scheduler state][split rows][V^T copy][row_ptr][col_idx]; the CSR entry point
+// uses the first three parts, the V^T one the first two. The scheduler part is sized for the largest n_xcd.
 constexpr int kMaxXcd = 64;
-size_t attn_sched_bytes(const Dims& d) { return align_up(wa::sched_state_ints(d.bh, d.mb, kMaxXcd) * 4); }
+size_t attn_order_bytes(const Dims& d) { return align_up(wa::sched_state_ints(d.bh, d.mb, kMaxXcd) * 4); }
+size_t attn_split_bytes(const Dims& d) {
+  const int cap = wa::split_cap(d.bh, d.mb, d.blk, d.d);
+  return cap > 0 ? align_up(wa::split_ints(cap) * 4 + cap * wa::part_tile_floats(d.blk, d.d) * 4) : 0;
+}
+size_t attn_sched_bytes(const Dims& d) { return attn_order_bytes(d) + attn_split_bytes(d); }
 size_t attn_csr_ws_bytes(const Dims& d) {
   return attn_sched_bytes(d) + align_up(wa_vt_bytes(d.bh, d.mb, d.d, d.blk));
 }
@@ -179,14 +184,17 @@ wa_status launch_compact(const uint8_t* mask, const Dims& d, int32_t* row_ptr, i
 }
 
 // v: V in its natural layout (transposed into the workspace after the scheduler state), or null with
-// vt: V already transposed by the caller.
-wa_status launch_attn(const void* q, const void* k, const void* v, const void* vt, void* ws, const int32_t* row_ptr,
-                      const int32_t* col_idx, const int32_t* perm, const int32_t* seg, const Dims& d, float scale,
-                      int32_t n_xcd, int32_t head_order, void* o, float* lse, int32_t* status, hipStream_t st) {
+// vt: V already transposed by the caller. split: the split rows' memory, attn_split_bytes(d).
+wa_status launch_attn(const void* q, const void* k, const void* v, const void* vt, void* ws, void* split,
+                      const int32_t* row_ptr, const int32_t* col_idx, const int32_t* perm, const int32_t* seg,
+                      const Dims& d, float scale, int32_t n_xcd, int32_t head_order, void* o, float* lse, int32_t* status, hipStream_t st) {
   WaAttnLaunch a{};
   a.q = q; a.k = k; a.v = v;
   a.sched = (int32_t*)ws;
   a.vt = v ? (void*)((char*)ws + attn_sched_bytes(d)) : const_cast<void*>(vt);
+  a.split_cap = wa::split_cap(d.bh, d.mb, d.blk, d.d);
+  a.split = (int32_t*)split;
+  a.part = (float*)(a.split + wa::split_ints(a.split_cap));
   a.row_ptr = row_ptr; a.col_idx = col_idx; a.perm = perm; a.seg = seg;
   a.o = o; a.lse = lse; a.status = status; a.head_order = head_order;
   a.bh = (int32_t)d.bh; a.seq_len = d.n; a.mb = d.mb; a.head_dim = d.d; a.block = d.blk; a.n_xcd = n_xcd;
@@ -440,8 +448,8 @@ wa_status wa_sparse_attn(const void* q, const void* k, const void* v, const uint
   int32_t* col_idx = (int32_t*)(base + attn_csr_ws_bytes(d) + align_up((size_t)d.bh * (d.mb + 1) * 4));
   s = launch_compact(mask, d, row_ptr, col_idx, st);
   if (s != WA_OK) return s;
-  s = launch_attn(q, k, v, nullptr, base, row_ptr, col_idx, perm, seg_start, d, softmax_scale, n_xcd, 0, o, lse,
-                  status, st);
+  s = launch_attn(q, k, v, nullptr, base, base + attn_order_bytes(d), row_ptr, col_idx, perm, seg_start, d,
+                  softmax_scale, n_xcd, 0, o, lse, status, st);
   if (s != WA_OK) return s;
   return ok();
 }
@@ -459,8 +467,8 @@ wa_status wa_sparse_attn_csr(const void* q, const void* k, const void* v, const 
   if (!row_ptr || !col_idx) return fail(WA_ERR_INVALID_ARG, "row_ptr and col_idx must be non-null");
   s = check_ws(workspace, workspace_bytes, attn_csr_ws_bytes(d));
   if (s != WA_OK) return s;
-  s = launch_attn(q, k, v, nullptr, workspace, row_ptr, col_idx, perm, seg_start, d, softmax_scale, n_xcd, 0, o, lse,
-                  status, (hipStream_t)stream);
+  s = launch_attn(q, k, v, nullptr, workspace, (char*)workspace + attn_order_bytes(d), row_ptr, col_idx, perm, seg_start,
+                  d, softmax_scale, n_xcd, 0, o, lse, status, (hipStream_t)stream);
   if (s != WA_OK) return s;
   return ok();
 }
@@ -484,12 +492,14 @@ wa_status wa_sparse_attn_vt_noalloc(const void* q, const void* k, const void* vt
     return fail(WA_ERR_WORKSPACE,
                 "scheduler state of %zu bytes (batch*heads %lld, M_B %d, n_xcd %d) exceeds the %d-byte static scratch",
                 need, (long long)d.bh, d.mb, options->n_xcd, WA_NOALLOC_SCRATCH_BYTES);
-  int32_t* scratch = nullptr;
-  size_t have = 0;
-  hipError_t e = wa_noalloc_scratch(&scratch, &have);
+  int32_t *scratch = nullptr, *split = nullptr;
+  size_t have = 0, have_split = 0;
+  hipError_t e = wa_noalloc_scratch(&scratch, &have, &split, &have_split);
   if (e != hipSuccess) return hip_fail(e, "static scratch lookup");
-  if (need > have) return fail(WA_ERR_WORKSPACE, "static scratch holds %zu bytes, %zu needed", have, need);
-  s = launch_attn(q, k, nullptr, vt, scratch, row_ptr, col_idx, perm, seg_start, d, options->softmax_scale,
+  if (need > have || attn_split_bytes(d) > have_split)
+    return fail(WA_ERR_WORKSPACE, "static scratch holds %zu + %zu bytes, %zu + %zu needed", have, have_split, need,
+                attn_split_bytes(d));
+  s = launch_attn(q, k, nullptr, vt, scratch, split, row_ptr, col_idx, perm, seg_start, d, options->softmax_scale,
                   options->n_xcd, options->head_order, o, lse, status, (hipStream_t)stream);
   if (s != WA_OK) return s;
   return ok();
@@ -530,8 +540,8 @@ wa_status wa_sparse_attn_vt(const void* q, const void* k, const void* vt, const 
   if (!row_ptr || !col_idx) return fail(WA_ERR_INVALID_ARG, "row_ptr and col_idx must be non-null");
   s = check_ws(workspace, workspace_bytes, attn_sched_bytes(d));
   if (s != WA_OK) return s;
-  s = launch_attn(q, k, nullptr, vt, workspace, row_ptr, col_idx, perm, seg_start, d, options->softmax_scale,
-                  options->n_xcd, options->head_order, o, lse, status, (hipStream_t)stream);
+  s = launch_attn(q, k, nullptr, vt, workspace, (char*)workspace + attn_order_bytes(d), row_ptr, col_idx, perm, seg_start,
+                  d, options->softmax_scale, options->n_xcd, options->head_order, o, lse, status, (hipStream_t)stream);
   if (s != WA_OK) return s;
   return ok();
 }

@@ -44,12 +44,14 @@
 // whose last task is a long row ends with every other workgroup idle; so the last
 // heads of each queue run in an order built at each call: a row that could still
 // be running once the rest of the queue is done starts first, longest first, and
-// every other row keeps its place (tail_order_kernel).
+// every other row keeps its place (tail_order). In a launch of few rows even that leaves the
+// longest row running alone, so rows of more than L blocks are computed in chunks (split_plan).
 
 #include "common.h"
 #include "wavealign.h"
 
 #include <algorithm>
+#include <atomic>
 #include <mutex>
 #include <type_traits>
 
@@ -144,6 +146,15 @@ __device__ __forceinline__ void dma16(const void* gbase, uint32_t voff, const un
       : "memory");
 }
 
+// A device-scope 16-byte store: it goes through to the level every XCD sees. The caller waits for its
+// completion (vmcnt) before it publishes the data. The instruction after a store of more than 8 bytes
+// must not write the registers of its data; the compiler does not look for that inside assembly.
+__device__ __forceinline__ void store_through(float* p, float x, float y, float z, float w) {
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  const f32x4 v = {x, y, z, w};
+  asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
+}
+
 // DMA geometry of a tile with rows of RB bytes copied by NW wavefronts: instruction i of wavefront w
 // writes tile rows [(i*NW + w)*RPI, +RPI), lane l the chunk (l mod LPR) of row (l / LPR) among them.
 // The global source of that slot is chunk swz(row, slot) of the row (each swizzle is an involution).
@@ -200,54 +211,121 @@ __device__ __forceinline__ void issue_vt(unsigned char* tile, const unsigned cha
           tile + (i * C::NW + w) * 1024);
 }
 
-// Next task of this workgroup: slot of a head from the queue of its XCD, else from the others.
-// Run by one lane; returns false when every queue is exhausted.
-__device__ bool fetch_task(const WaAttnLaunch& a, int home, int* bh_out, int* slot_out) {
-  int32_t* cnt = a.sched;
-  const int32_t* pre = a.sched + 64;
-  const int th = wa::tail_heads(a.bh, a.mb);
-  for (int k = 0; k < a.n_xcd; ++k) {
-    const int x = (home + k) % a.n_xcd;
-    const int32_t* px = pre + (int64_t)x * (a.bh + 1);
-    const int total = px[a.bh];
-    if (__hip_atomic_load(cnt + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= total) continue;
-    const int t = atomicAdd(cnt + x, 1);
-    if (t >= total) continue;
-    if (a.head_order) {  // round-robin over the heads: the call's order table
-      const int32_t* ilv = a.sched + wa::ilv_offset(a.bh, a.mb, a.n_xcd);
-      const int ent = ilv[64 + ilv[x] + t];
-      *bh_out = ent / a.mb;
-      *slot_out = ent - *bh_out * a.mb;
-      return true;
-    }
-    const int tb = px[a.bh - th];
+// The attention kernel reads its arguments where they are used, through the kernel-argument pointer
+// made opaque at that point: hoisted out of the task loop they would hold some 40 scalar registers,
+// which the compiler then spills into vector registers that the block loop needs.
+typedef const __attribute__((address_space(4))) WaAttnLaunch* Args;
+__device__ __forceinline__ Args kernel_args() {
+  Args a = (Args)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(a));
+  return a;
+}
+
+// What a workgroup computes next: chunk `chunk` of the `chunks` chunks of a row's list (1: the whole
+// row), list entries [beg, end).
+struct Task {
+  int32_t bh, row, beg, end, chunks, chunk, tile;
+};
+
+// The first task of workgroup b is fixed: the chunks of the split rows go to workgroups 0, 1, ..., and the
+// first entries of queue x to the workgroups after them with b mod n_xcd = x, in order. Only later
+// tasks are taken with atomic counters: an atomic on one address costs about 0.1 us of device time,
+// whoever issues it, so a launch whose 512 to 1,536 workgroups all began with one spent 50 us and more.
+__device__ __forceinline__ int first_wg(int x, int split, int n_xcd) {  // of queue x's first entry
+  return split + (x + n_xcd - split % n_xcd) % n_xcd;
+}
+
+// Entry t of queue x as a task; false if it needs no work (an invalid perm entry, which is reported, or a
+// row computed in chunks).
+__device__ bool queue_task(Args a, int x, int t, int longest, Task* out) {
+  const int32_t* px = a->sched + 64 + (int64_t)x * (a->bh + 1);
+  const int th = wa::tail_heads(a->bh, a->mb);
+  int bh, slot;
+  if (a->head_order) {  // round-robin over the heads: the call's order table
+    const int32_t* ilv = a->sched + wa::ilv_offset(a->bh, a->mb, a->n_xcd);
+    const int ent = ilv[64 + ilv[x] + t];
+    bh = ent / a->mb;
+    slot = ent - bh * a->mb;
+  } else {
+    const int tb = px[a->bh - th];
     if (t >= tb) {  // the last heads: the call's tail order
-      const int e = a.sched[wa::tail_offset(a.bh, a.n_xcd) + (int64_t)x * th * a.mb + (t - tb)];
-      *bh_out = a.bh - th + (e >> 16);
-      *slot_out = e & 0xFFFF;
-      return true;
+      const int e = a->sched[wa::tail_offset(a->bh, a->n_xcd) + (int64_t)x * th * a->mb + (t - tb)];
+      bh = a->bh - th + (e >> 16);
+      slot = e & 0xFFFF;
+    } else {
+      // head h with px[h] <= t < px[h+1]: with segments of about equal length its share of the queue
+      // tells, else a binary search
+      bh = (int)((int64_t)t * a->bh / px[a->bh]);
+      if (px[bh] > t || px[bh + 1] <= t) {
+        int lo = 0, hi = a->bh - 1;
+        while (lo < hi) {
+          const int mid = (lo + hi + 1) >> 1;
+          if (px[mid] <= t) lo = mid; else hi = mid - 1;
+        }
+        bh = lo;
+      }
+      int s0, s1;
+      wa::xcd_segment(x, a->mb, a->n_xcd, a->seg ? a->seg + (int64_t)bh * (a->n_xcd + 1) : nullptr, &s0, &s1);
+      slot = s0 + (t - px[bh]);
     }
-    // head h with px[h] <= t < px[h+1]
-    int lo = 0, hi = a.bh - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (px[mid] <= t) lo = mid; else hi = mid - 1;
-    }
-    int s0, s1;
-    wa::xcd_segment(x, a.mb, a.n_xcd, a.seg ? a.seg + (int64_t)lo * (a.n_xcd + 1) : nullptr, &s0, &s1);
-    *bh_out = lo;
-    *slot_out = s0 + (t - px[lo]);
-    return true;
   }
-  return false;
+  const int row = a->perm ? a->perm[(int64_t)bh * a->mb + slot] : slot;
+  if ((unsigned)row >= (unsigned)a->mb) {  // not a valid block index: nothing to compute, reported
+    if (a->status) atomicOr(a->status, 1);
+    return false;
+  }
+  const int32_t* rp = a->row_ptr + (int64_t)bh * (a->mb + 1) + row;
+  const int beg = rp[0], end = rp[1];
+  *out = {bh, row, beg, end, 1, 0, 0};
+  return end - beg <= longest;
+}
+
+__device__ void split_task(Args a, int k, Task* out) {
+  const int4 e = ((const int4*)(a->split + 64))[k];
+  const int32_t* rp = a->row_ptr + (int64_t)e.x * (a->mb + 1) + e.y;
+  const int n = rp[1] - rp[0], c = e.z & 0xFFFF, chunks = e.z >> 16;
+  *out = {e.x, e.y, rp[0] + (int)((int64_t)n * c / chunks), rp[0] + (int)((int64_t)n * (c + 1) / chunks), chunks, c, e.w};
+}
+
+// Next task of this workgroup, run by one lane: the chunks of the split rows first (the longest work),
+// then the queue of the workgroup's XCD, then the others. bh = -1 when nothing is left.
+__device__ void fetch_task(Args a, bool first, Task* t) {
+  const int b = blockIdx.x, wgs = gridDim.x;
+  const int split = a->split_cap > 0 ? a->split[0] : 0;
+  const int longest = split > 0 ? a->split[2] : INT32_MAX;  // rows of more blocks are split
+  const int32_t* pre = a->sched + 64;
+  if (first) {
+    if (b < split) return split_task(a, b, t);
+    const int x = b % a->n_xcd, k = (b - first_wg(x, split, a->n_xcd)) / a->n_xcd;
+    if (k < pre[(int64_t)x * (a->bh + 1) + a->bh] && queue_task(a, x, k, longest, t)) return;
+  }
+  if (split > wgs) {
+    const int k = wgs + atomicAdd(a->split + 1, 1);
+    if (k < split) return split_task(a, k, t);
+  }
+  const int home = (int)(__builtin_amdgcn_s_getreg((3 << 11) | (0 << 6) | 20) & 0xF) % a->n_xcd;
+  for (int i = 0; i < a->n_xcd; ++i) {
+    const int x = (home + i) % a->n_xcd;
+    const int total = pre[(int64_t)x * (a->bh + 1) + a->bh];
+    const int w0 = first_wg(x, split, a->n_xcd);
+    const int given = w0 < wgs ? (wgs - w0 + a->n_xcd - 1) / a->n_xcd : 0;  // entries with a fixed workgroup
+    if (given >= total) continue;
+    int32_t* cnt = a->sched + x;
+    while (given + __hip_atomic_load(cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < total) {
+      const int k = given + atomicAdd(cnt, 1);
+      if (k >= total) break;
+      if (queue_task(a, x, k, longest, t)) return;
+    }
+  }
+  t->bh = -1;
 }
 
 template <int D, int BLK>
-__global__ __launch_bounds__(BLK * 2, 2) void attn_fwd_kernel(WaAttnLaunch a) {
+__global__ __launch_bounds__(BLK * 2, 2) void attn_fwd_kernel(WaAttnLaunch) {
   using C = Cfg<D, BLK>;
   __shared__ __attribute__((aligned(1024))) unsigned char k_lds[C::TBYTES];
   __shared__ __attribute__((aligned(1024))) unsigned char v_lds[C::TBYTES];
-  __shared__ int task[2];
+  __shared__ Task task;
   __shared__ int redo;  // the current row is recomputed against its exact maximum
 
   const int tid = threadIdx.x;
@@ -255,10 +333,6 @@ __global__ __launch_bounds__(BLK * 2, 2) void attn_fwd_kernel(WaAttnLaunch a) {
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform within the wavefront
   const int l32 = lane & 31;
   const int hf = lane >> 5;
-  const int n = a.seq_len;
-  const float c2 = a.scale * kLog2e;
-
-  const int home = (int)(__builtin_amdgcn_s_getreg((3 << 11) | (0 << 6) | 20) & 0xF) % a.n_xcd;
   // byte offsets of this lane's K-operand chunk of k-step s in the K tile (key tile kt adds kt 32 RB)
   uint32_t kofs[C::KS];
   {
@@ -275,37 +349,37 @@ __global__ __launch_bounds__(BLK * 2, 2) void attn_fwd_kernel(WaAttnLaunch a) {
       vofs[ks] = (uint32_t)(kr * C::VRB + swz_k<C::VRB>(kr, 2 * ks + hf) * 16);
   }
 
-  for (;;) {
+  for (bool first = true;; first = false) {
     if (tid == 0) {
-      int tb = -1, ts = 0;
-      if (!fetch_task(a, home, &tb, &ts)) tb = -1;
-      task[0] = tb;
-      task[1] = ts;
+      Task t;
+      fetch_task(kernel_args(), first, &t);
+      task = t;
       redo = 0;
     }
     __syncthreads();
-    const int bh = __builtin_amdgcn_readfirstlane(task[0]);
-    const int slot = __builtin_amdgcn_readfirstlane(task[1]);
+    const int bh = __builtin_amdgcn_readfirstlane(task.bh);
+    const int row = __builtin_amdgcn_readfirstlane(task.row);
+    const int beg = __builtin_amdgcn_readfirstlane(task.beg);
+    const int end = __builtin_amdgcn_readfirstlane(task.end);
+    const int chunks = __builtin_amdgcn_readfirstlane(task.chunks);
+    const int tile = __builtin_amdgcn_readfirstlane(task.tile);    // the row's first partial tile
+    const int chunk = __builtin_amdgcn_readfirstlane(task.chunk);
     __syncthreads();  // every wavefront has read the task before it is overwritten
     if (bh < 0) break;
-    const int row = a.perm ? a.perm[(int64_t)bh * a.mb + slot] : slot;
-    if ((unsigned)row >= (unsigned)a.mb) {  // not a valid block index: nothing to compute, reported
-      if (tid == 0 && a.status) atomicOr(a.status, 1);
-      continue;
-    }
 
-    const uint16_t* qg = (const uint16_t*)a.q + (int64_t)bh * n * D;
-    const unsigned char* kg = (const unsigned char*)a.k + (int64_t)bh * n * D * 2;
-    const int64_t npad = (int64_t)a.mb * BLK;
-    const unsigned char* vtg = (const unsigned char*)a.vt + (int64_t)bh * D * npad * 2;
+    const Args a = kernel_args();
+    const int n = a->seq_len;
+    const int mb = a->mb;
+    const float c2 = a->scale * kLog2e;
+    const uint16_t* qg = (const uint16_t*)a->q + (int64_t)bh * n * D;
+    const unsigned char* kg = (const unsigned char*)a->k + (int64_t)bh * n * D * 2;
+    const int64_t npad = (int64_t)mb * BLK;
+    const unsigned char* vtg = (const unsigned char*)a->vt + (int64_t)bh * D * npad * 2;
     const uint32_t vt_row_bytes = (uint32_t)(npad * 2);
 
-    const int32_t* rp = a.row_ptr + (int64_t)bh * (a.mb + 1);
-    const int beg = rp[row];
-    const int end = rp[row + 1];
     // read-only for the whole kernel: the constant address space lets the list be read with scalar loads
     typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
-    const const_i32_ptr cols = (const_i32_ptr)(a.col_idx + (int64_t)bh * a.mb * a.mb);
+    const const_i32_ptr cols = (const_i32_ptr)(a->col_idx + (int64_t)bh * mb * mb);
 
     // Q columns of this wavefront: B operand of S^T = K Q^T
     const int qi = row * BLK + w * 32 + l32;
@@ -388,7 +462,7 @@ __global__ __launch_bounds__(BLK * 2, 2) void attn_fwd_kernel(WaAttnLaunch a) {
       int j_next = 0;
       if (has_next) {
         j_next = cols[e + 1];
-        if ((unsigned)j_next >= (unsigned)a.mb) {  // invalid KV index: block 0 is read, reported
+        if ((unsigned)j_next >= (unsigned)mb) {  // invalid KV index: block 0 is read, reported
           j_next = 0;
           bad_kv = 1;
         }
@@ -454,7 +528,7 @@ __global__ __launch_bounds__(BLK * 2, 2) void attn_fwd_kernel(WaAttnLaunch a) {
       if (has_next) issue_vt<D, BLK>(v_lds, vtg, vt_row_bytes, j_next * BLK, w, lane_o);
       j_cur = j_next;
     };
-    const bool ragged_last = end > beg && (n % BLK) != 0 && cols[end - 1] == a.mb - 1;
+    const bool ragged_last = end > beg && (n % BLK) != 0 && cols[end - 1] == mb - 1;
     const int e_plain = end - (ragged_last ? 1 : 0);
 
     // Pass 0 takes the first block's maximum as the reference. If some probability reached
@@ -465,7 +539,7 @@ __global__ __launch_bounds__(BLK * 2, 2) void attn_fwd_kernel(WaAttnLaunch a) {
     for (int pass = 0;; ++pass) {
       if (beg < end) {
         j_cur = cols[beg];
-        if ((unsigned)j_cur >= (unsigned)a.mb) {
+        if ((unsigned)j_cur >= (unsigned)mb) {
           j_cur = 0;
           bad_kv = 1;
         }
@@ -505,7 +579,7 @@ __global__ __launch_bounds__(BLK * 2, 2) void attn_fwd_kernel(WaAttnLaunch a) {
       float mx = -INFINITY;
       for (int e2 = beg; e2 < end; ++e2) {
         int j = cols[e2];
-        if ((unsigned)j >= (unsigned)a.mb) j = 0;
+        if ((unsigned)j >= (unsigned)mb) j = 0;
         issue_tile<D, BLK, false>(k_lds, kg, j * BLK, n, w, lane);
         WA_WAIT_VM(0);
         WA_BARRIER();
@@ -518,11 +592,103 @@ __global__ __launch_bounds__(BLK * 2, 2) void attn_fwd_kernel(WaAttnLaunch a) {
       m_run = mx;
     }
 
-    // ---- epilogue: normalise and store at the original rows ----
+    // ---- epilogue: merge the chunks of a split row, normalise and store at the original rows ----
     const float ltot = l_run + __shfl_xor(l_run, 32);
+    if (chunks > 1) {
+      // the thread's offsets from an opaque copy of its index, so that none is held across the block loop
+      int tid_o = tid;
+      asm volatile("" : "+v"(tid_o));
+      const Args a = kernel_args();
+      const int hf_o = (tid_o >> 5) & 1;
+      const int qloc = (tid_o >> 6) * 32 + (tid_o & 31);
+      const int qi_o = row * BLK + qloc;
+      // Partial tile of this chunk: O in 16-byte pieces [register quad][thread], then the row maxima and
+      // the row sums. Device-scope stores (they go through to the level every XCD sees), completed before
+      // the arrival is counted; the last arrival acquires and merges every tile in chunk order.
+      constexpr int NQ = C::DT * 4;
+      const size_t tile_floats = wa::part_tile_floats(BLK, D);
+      float* mine = a->part + (size_t)(tile + chunk) * tile_floats;
+#pragma unroll
+      for (int r = 0; r < NQ; ++r)
+        store_through(mine + 4 * (r * C::NT + tid_o), oacc[r >> 2][4 * (r & 3)], oacc[r >> 2][4 * (r & 3) + 1],
+                      oacc[r >> 2][4 * (r & 3) + 2], oacc[r >> 2][4 * (r & 3) + 3]);
+      if (hf_o == 0) {
+        __hip_atomic_store(mine + BLK * D + qloc, m_run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(mine + BLK * D + BLK + qloc, ltot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      if (bad_kv && tid == 0 && a->status) atomicOr(a->status, 2);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+      if (tid == 0) redo = atomicAdd(a->split + wa::split_arrival(a->split_cap, tile), 1);
+      __syncthreads();
+      const int arrived = __builtin_amdgcn_readfirstlane(redo);
+      __syncthreads();  // every wavefront has read the count before the next task clears it
+      if (arrived != chunks - 1) continue;
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+      const float* first = a->part + (size_t)tile * tile_floats;
+      const int qrow = BLK * D + qloc;
+      // Each step reads the pieces of MC chunks together (a serial walk over the chunks costs a memory
+      // latency each); past the last chunk, the last one again with weight 0.
+      constexpr int MC = 4;
+      auto at = [&](int c) { return first + (size_t)min(c, chunks - 1) * tile_floats; };
+      float m = -INFINITY, l = 0.f;
+      for (int c0 = 0; c0 < chunks; c0 += 2 * MC) {
+        float u[2 * MC];
+#pragma unroll
+        for (int c = 0; c < 2 * MC; ++c) u[c] = at(c0 + c)[qrow];
+#pragma unroll
+        for (int c = 0; c < 2 * MC; ++c) m = fmaxf(m, u[c]);
+      }
+      float inv = 0.f;
+      uint16_t* og = (uint16_t*)a->o + ((int64_t)bh * n + qi_o) * D + 8 * hf_o;
+#pragma unroll 1
+      for (int g = 0; g < 2 * C::DT; g += 2) {  // 2 x 8 consecutive columns of this lane
+        float acc[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) acc[j] = 0.f;
+        l = 0.f;
+#pragma unroll 1
+        for (int c0 = 0; c0 < chunks; c0 += MC) {
+          float4 u[MC][4];
+          float um[MC], ul[MC];
+#pragma unroll
+          for (int c = 0; c < MC; ++c) {
+            const float* pt = at(c0 + c);
+            um[c] = pt[qrow];
+            ul[c] = pt[qrow + BLK];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) u[c][j] = ((const float4*)pt)[(2 * g + j) * C::NT + tid_o];
+          }
+#pragma unroll
+          for (int c = 0; c < MC; ++c) {
+            const float wgt = c0 + c < chunks ? __builtin_amdgcn_exp2f(um[c] - m) : 0.f;
+            l += wgt * ul[c];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              acc[4 * j] += wgt * u[c][j].x;
+              acc[4 * j + 1] += wgt * u[c][j].y;
+              acc[4 * j + 2] += wgt * u[c][j].z;
+              acc[4 * j + 3] += wgt * u[c][j].w;
+            }
+          }
+        }
+        inv = l > 0.f ? 1.f / l : 0.f;
+        if (qi_o < n)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            *(uint4*)(og + 16 * (g + j)) =
+                make_uint4(pack_bf16x2(acc[8 * j] * inv, acc[8 * j + 1] * inv),
+                           pack_bf16x2(acc[8 * j + 2] * inv, acc[8 * j + 3] * inv),
+                           pack_bf16x2(acc[8 * j + 4] * inv, acc[8 * j + 5] * inv),
+                           pack_bf16x2(acc[8 * j + 6] * inv, acc[8 * j + 7] * inv));
+      }
+      if (a->lse && hf_o == 0 && qi_o < n) a->lse[(int64_t)bh * n + qi_o] = l > 0.f ? (m + __log2f(l)) * kLn2 : -INFINITY;
+      continue;
+    }
     const float inv = ltot > 0.f ? 1.f / ltot : 0.f;
+    const Args ae = kernel_args();
     if (qi < n) {
-      uint16_t* og = (uint16_t*)a.o + ((int64_t)bh * n + qi) * D;
+      uint16_t* og = (uint16_t*)ae->o + ((int64_t)bh * n + qi) * D;
 #pragma unroll
       for (int dt = 0; dt < C::DT; ++dt)
 #pragma unroll
@@ -535,251 +701,10 @@ __global__ __launch_bounds__(BLK * 2, 2) void attn_fwd_kernel(WaAttnLaunch a) {
           st.w = pack_bf16x2(oacc[dt][8 * h2 + 6] * inv, oacc[dt][8 * h2 + 7] * inv);
           *(uint4*)(og + col) = st;
         }
-      if (a.lse && hf == 0)
-        a.lse[(int64_t)bh * n + qi] = ltot > 0.f ? (m_run + __log2f(ltot)) * kLn2 : -INFINITY;
+      if (ae->lse && hf == 0)
+        ae->lse[(int64_t)bh * n + qi] = ltot > 0.f ? (m_run + __log2f(ltot)) * kLn2 : -INFINITY;
     }
-    if (bad_kv && tid == 0 && a.status) atomicOr(a.status, 2);
-  }
-}
-
-// Scheduler set-up: zero the queue counters and the status word, and build, per queue, the prefix
-// sums of its segment lengths over the heads. One workgroup; thread x handles queue x.
-__global__ __launch_bounds__(64) void sched_kernel(int32_t* sched, const int32_t* seg, int32_t* status, int bh,
-                                                   int mb, int n_xcd) {
-  const int x = threadIdx.x;
-  if (x == 0 && status) *status = 0;
-  if (x >= n_xcd) return;
-  sched[x] = 0;
-  int32_t* px = sched + 64 + (int64_t)x * (bh + 1);
-  int acc = 0;
-  px[0] = 0;
-  for (int h = 0; h < bh; ++h) {
-    int s0, s1;
-    wa::xcd_segment(x, mb, n_xcd, seg ? seg + (int64_t)h * (n_xcd + 1) : nullptr, &s0, &s1);
-    acc += s1 - s0;
-    px[h + 1] = acc;
-  }
-}
-
-// Tail order of queue x (one workgroup per queue): entries e = 0, 1, ... enumerate, in queue order,
-// the slots of segment x of the last th heads. A row of n blocks that starts with fewer than
-// 2 n (grid / n_xcd) blocks queued after it could outlast the rest of the queue; such rows go first,
-// by descending n (ties in queue order), and the others follow in queue order. Each entry is
-// (head offset << 16) | slot. The order is a permutation of the queue's slots, so every row still
-// runs exactly once.
-__global__ __launch_bounds__(1024) void tail_order_kernel(WaAttnLaunch a, int grid) {
-  constexpr int NT = 1024;
-  constexpr int PER = wa::kTailEntries / NT;
-  __shared__ int32_t hstart[wa::kTailMaxHeads + 1];  // first entry of each head's segment
-  __shared__ int32_t hslot0[wa::kTailMaxHeads];      // its first slot
-  __shared__ int32_t part[NT];
-  __shared__ uint32_t key[wa::kTailEntries];
-  const int x = blockIdx.x;
-  const int t = threadIdx.x;
-  const int th = wa::tail_heads(a.bh, a.mb);
-  const int hb = a.bh - th;
-  int32_t* tail = a.sched + wa::tail_offset(a.bh, a.n_xcd) + (int64_t)x * th * a.mb;
-  if (t < th) {
-    int s0, s1;
-    wa::xcd_segment(x, a.mb, a.n_xcd, a.seg ? a.seg + (int64_t)(hb + t) * (a.n_xcd + 1) : nullptr, &s0, &s1);
-    hslot0[t] = s0;
-    part[t] = s1 - s0;
-  }
-  __syncthreads();
-  if (t == 0) {
-    int acc = 0;
-    for (int k = 0; k < th; ++k) {
-      hstart[k] = acc;
-      acc += part[k];
-    }
-    hstart[th] = acc;
-  }
-  __syncthreads();
-  const int total = hstart[th];
-  // head offset of entry e: the last k with hstart[k] <= e
-  auto head_of = [&](int e) {
-    int lo = 0, hi = th - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (hstart[mid] <= e) lo = mid; else hi = mid - 1;
-    }
-    return lo;
-  };
-  // block counts of this thread's entries PER t .. PER t + PER - 1 (independent loads first)
-  int row[PER], nb[PER];
-  const int e0 = t * PER;
-  int k = e0 < total ? head_of(e0) : 0;
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int e = e0 + i;
-    row[i] = -1;
-    if (e < total) {
-      while (e >= hstart[k + 1]) ++k;
-      const int slot = hslot0[k] + (e - hstart[k]);
-      row[i] = a.perm ? a.perm[(int64_t)(hb + k) * a.mb + slot] : slot;
-    }
-  }
-  k = e0 < total ? head_of(e0) : 0;
-  int sum = 0;
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int e = e0 + i;
-    nb[i] = 0;
-    if (e < total) {
-      while (e >= hstart[k + 1]) ++k;
-      if ((unsigned)row[i] < (unsigned)a.mb) {
-        const int32_t* rp = a.row_ptr + (int64_t)(hb + k) * (a.mb + 1);
-        nb[i] = min(max(rp[row[i] + 1] - rp[row[i]], 0), WA_MAX_BLOCKS);
-      }
-    }
-    sum += nb[i];
-  }
-  // blocks queued after each entry, then the late entries and their ranks (block-wide scans)
-  auto block_scan = [&](int v, int* all) {  // inclusive prefix sum over the threads, and the total
-    part[t] = v;
-    __syncthreads();
-    for (int off = 1; off < NT; off <<= 1) {
-      const int u = t >= off ? part[t - off] : 0;
-      __syncthreads();
-      part[t] += u;
-      __syncthreads();
-    }
-    const int r = part[t];
-    *all = part[NT - 1];
-    __syncthreads();
-    return r;
-  };
-  const int64_t wgs = max(grid / a.n_xcd, 1);
-  int all = 0;
-  const int incl = block_scan(sum, &all);
-  int64_t after = (int64_t)all - incl;  // blocks of the entries after this thread's
-  uint32_t late_bits = 0;
-  int nlate_mine = 0;
-#pragma unroll
-  for (int i = PER - 1; i >= 0; --i) {
-    const int e = e0 + i;
-    if (e < total && 2 * (int64_t)nb[i] * wgs > after) {
-      late_bits |= 1u << i;
-      ++nlate_mine;
-    }
-    after += nb[i];
-  }
-  int nlate = 0;
-  const int late_incl = block_scan(nlate_mine, &nlate);
-  int late_before = late_incl - nlate_mine;
-  int P = 1;
-  while (P < nlate) P <<= 1;
-  for (int i = t; i < P; i += NT) key[i] = 0xFFFFFFFFu;
-  __syncthreads();
-  k = e0 < total ? head_of(e0) : 0;
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int e = e0 + i;
-    if (e < total) {
-      while (e >= hstart[k + 1]) ++k;
-      if (late_bits >> i & 1u) {
-        key[late_before++] = ((uint32_t)(WA_MAX_BLOCKS - nb[i]) << 14) | (uint32_t)e;
-      } else {
-        tail[nlate + (e - late_before)] = (k << 16) | (hslot0[k] + (e - hstart[k]));
-      }
-    }
-  }
-  __syncthreads();
-  // late entries: bitonic sort ascending = descending block count, ties in queue order
-  for (int kk = 2; kk <= P; kk <<= 1)
-    for (int j = kk >> 1; j > 0; j >>= 1) {
-      for (int i = t; i < P; i += NT) {
-        const int l = i ^ j;
-        if (l > i) {
-          const uint32_t u = key[i], v = key[l];
-          if ((u > v) == ((i & kk) == 0)) {
-            key[i] = v;
-            key[l] = u;
-          }
-        }
-      }
-      __syncthreads();
-    }
-  for (int i = t; i < nlate; i += NT) {
-    const int e = (int)(key[i] & 0x3FFFu);
-    const int kh = head_of(e);
-    tail[i] = (kh << 16) | (hslot0[kh] + (e - hstart[kh]));
-  }
-}
-
-// Head-interleaved order of queue x (one workgroup per queue): the queue's tasks round-robin over the
-// heads, round r taking slot s0_h + r of every head h whose segment of the queue has more than r
-// slots, heads ascending. Entry (h, r) therefore sits at C(r) + #{h' < h : L_h' > r}, with L_h the
-// segment length and C(r) = sum_h min(L_h, r) the entries of the rounds before r. Entries are
-// h * mb + slot; queue x's entries start at the total of queues 0..x-1 (ilv[x]).
-__global__ __launch_bounds__(1024) void ilv_order_kernel(WaAttnLaunch a) {
-  constexpr int NT = 1024;
-  constexpr int RPT = WA_MAX_BLOCKS / NT;  // rounds per thread: r = t + k NT < mb <= WA_MAX_BLOCKS
-  __shared__ int off_s;
-  const int x = blockIdx.x;
-  const int t = threadIdx.x;
-  int32_t* ilv = a.sched + wa::ilv_offset(a.bh, a.mb, a.n_xcd);
-  if (t == 0) {
-    int off = 0;
-    for (int y = 0; y < x; ++y) off += a.sched[64 + (int64_t)y * (a.bh + 1) + a.bh];
-    ilv[x] = off;
-    off_s = off;
-  }
-  __syncthreads();
-  int32_t* out = ilv + 64 + off_s;
-  int c[RPT];
-#pragma unroll
-  for (int k = 0; k < RPT; ++k) c[k] = 0;
-  for (int h = 0; h < a.bh; ++h) {
-    int s0, s1;
-    wa::xcd_segment(x, a.mb, a.n_xcd, a.seg ? a.seg + (int64_t)h * (a.n_xcd + 1) : nullptr, &s0, &s1);
-#pragma unroll
-    for (int k = 0; k < RPT; ++k) c[k] += min(s1 - s0, t + k * NT);
-  }
-  for (int h = 0; h < a.bh; ++h) {
-    int s0, s1;
-    wa::xcd_segment(x, a.mb, a.n_xcd, a.seg ? a.seg + (int64_t)h * (a.n_xcd + 1) : nullptr, &s0, &s1);
-#pragma unroll
-    for (int k = 0; k < RPT; ++k) {
-      const int r = t + k * NT;
-      if (r < s1 - s0) out[c[k]++] = h * a.mb + s0 + r;
-    }
-  }
-}
-
-// V [bh][n][D] -> V^T [bh][D][npad], zero for keys >= n. One 64-key x 64-column tile per workgroup,
-// 16-byte loads and stores, transposed through LDS.
-template <int D>
-__global__ __launch_bounds__(256) void transpose_v_kernel(const uint16_t* __restrict__ v, uint16_t* __restrict__ vt,
-                                                         int n, int64_t npad, int tiles_n) {
-  __shared__ uint16_t t[64][64 + 8];
-  const int tile = blockIdx.x % tiles_n;
-  const int dtile = (blockIdx.x / tiles_n) % (D / 64);
-  const int64_t bh = blockIdx.x / ((int64_t)tiles_n * (D / 64));
-  const int key0 = tile * 64, d0 = dtile * 64;
-  const uint16_t* src = v + bh * n * D;
-  uint16_t* dst = vt + bh * D * npad;
-  const int tid = threadIdx.x;
-  // load: thread -> (key r, 8-column group c8), two passes of 32 keys
-#pragma unroll
-  for (int pass = 0; pass < 2; ++pass) {
-    const int r = pass * 32 + tid / 8, c8 = tid % 8;
-    uint4 val = make_uint4(0, 0, 0, 0);
-    if (key0 + r < n) val = *(const uint4*)(src + (int64_t)(key0 + r) * D + d0 + c8 * 8);
-    const uint32_t wv[4] = {val.x, val.y, val.z, val.w};
-#pragma unroll
-    for (int e = 0; e < 8; ++e) t[r][c8 * 8 + e] = (uint16_t)(wv[e >> 1] >> ((e & 1) * 16));
-  }
-  __syncthreads();
-  // store: thread -> (column d, 8-key group k8), two passes of 32 columns
-#pragma unroll
-  for (int pass = 0; pass < 2; ++pass) {
-    const int d = pass * 32 + tid / 8, k8 = tid % 8;
-    uint32_t wv[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      wv[e] = (uint32_t)t[k8 * 8 + 2 * e][d] | ((uint32_t)t[k8 * 8 + 2 * e + 1][d] << 16);
-    *(uint4*)(dst + (int64_t)(d0 + d) * npad + key0 + k8 * 8) = make_uint4(wv[0], wv[1], wv[2], wv[3]);
+    if (bad_kv && tid == 0 && ae->status) atomicOr(ae->status, 2);
   }
 }
 
@@ -795,47 +720,33 @@ int resident_cus() {
   return cached[dev];
 }
 
-template <int D>
-hipError_t launch_transpose(const void* v, void* vt, int64_t bh, int n, int mb, int blk, hipStream_t stream) {
-  const int64_t npad = (int64_t)mb * blk;
-  const int tiles_n = (int)((npad + 63) / 64);
-  const int64_t tgrid = bh * (D / 64) * tiles_n;
-  if (tgrid <= 0) return hipSuccess;
-  hipLaunchKernelGGL((transpose_v_kernel<D>), dim3((unsigned)tgrid), dim3(256), 0, stream, (const uint16_t*)v,
-                     (uint16_t*)vt, n, npad, tiles_n);
-  return hipGetLastError();
+// Workgroups of the attention kernel resident on one compute unit (looked up once per device).
+template <int D, int BLK>
+hipError_t occ_t(int* n) {
+  static std::atomic<int> cached[64];
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const bool keep = dev >= 0 && dev < 64;
+  if (keep && (*n = cached[dev].load(std::memory_order_relaxed)) > 0) return hipSuccess;
+  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(n, attn_fwd_kernel<D, BLK>, BLK * 2, 0);
+  if (e == hipSuccess && keep) cached[dev].store(*n, std::memory_order_relaxed);
+  return e;
 }
 
 template <int D, int BLK>
 hipError_t launch_t(const WaAttnLaunch& a, hipStream_t stream) {
-  hipLaunchKernelGGL(sched_kernel, dim3(1), dim3(64), 0, stream, a.sched, a.seg, a.status, a.bh, a.mb, a.n_xcd);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
   const int64_t tasks = (int64_t)a.bh * a.mb;
   int occ = 0;
-  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, attn_fwd_kernel<D, BLK>, BLK * 2, 0);
+  hipError_t e = occ_t<D, BLK>(&occ);
   if (e != hipSuccess) return e;
-  const int64_t grid = std::min<int64_t>(tasks, (int64_t)resident_cus() * std::max(occ, 1));
-  if (tasks > 0) {
-    if (a.head_order) {
-      hipLaunchKernelGGL(ilv_order_kernel, dim3(a.n_xcd), dim3(1024), 0, stream, a);
-    } else {
-      hipLaunchKernelGGL(tail_order_kernel, dim3(a.n_xcd), dim3(1024), 0, stream, a, (int)grid);
-    }
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  if (a.v) {  // V given in its natural layout: the call's transposed copy
-    e = launch_transpose<D>(a.v, a.vt, a.bh, a.seq_len, a.mb, BLK, stream);
-    if (e != hipSuccess) return e;
-  }
-  if (tasks <= 0) return hipSuccess;
-  hipLaunchKernelGGL((attn_fwd_kernel<D, BLK>), dim3((unsigned)grid), dim3(BLK * 2), 0, stream, a);
+  const int64_t slots = (int64_t)resident_cus() * std::max(occ, 1);
+  const int64_t grid = std::min<int64_t>(tasks, slots);
+  if ((e = wa_launch_attn_prep(a, (int)grid, (int)slots, stream)) != hipSuccess || tasks <= 0) return e;
+  // split rows give work to every resident workgroup, however few the rows
+  hipLaunchKernelGGL((attn_fwd_kernel<D, BLK>), dim3((unsigned)(a.split_cap > 0 ? slots : grid)), dim3(BLK * 2), 0,
+                     stream, a);
   return hipGetLastError();
-}
-
-template <int D, int BLK>
-hipError_t occ_t(int* n) {
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, attn_fwd_kernel<D, BLK>, BLK * 2, 0);
 }
 
 }  // namespace
@@ -845,10 +756,14 @@ hipError_t occ_t(int* n) {
 // address: its device address is looked up once per device (with that device current) and cached.
 static constexpr size_t kNoAllocInts = WA_NOALLOC_SCRATCH_BYTES / 4;
 static __device__ __align__(256) int32_t scratch[kNoAllocInts];
+// Its split rows (tasks, arrival counters and partial tiles) have an array of their own.
+static constexpr size_t kNoAllocSplitInts = wa::kPartBytes / 4 + 65536;
+static __device__ __align__(256) int32_t split_scratch[kNoAllocSplitInts];
 static std::mutex g_scratch_mu;
 static int32_t* g_scratch_ptr[64];
+static int32_t* g_split_ptr[64];
 
-hipError_t wa_noalloc_scratch(int32_t** ptr, size_t* bytes) {
+hipError_t wa_noalloc_scratch(int32_t** ptr, size_t* bytes, int32_t** split, size_t* split_bytes) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
@@ -859,10 +774,17 @@ hipError_t wa_noalloc_scratch(int32_t** ptr, size_t* bytes) {
     e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
     if (e != hipSuccess) return e;
     if (!p) return hipErrorInvalidSymbol;
+    void* sp = nullptr;
+    e = hipGetSymbolAddress(&sp, HIP_SYMBOL(split_scratch));
+    if (e != hipSuccess) return e;
+    if (!sp) return hipErrorInvalidSymbol;
+    g_split_ptr[dev] = (int32_t*)sp;
     g_scratch_ptr[dev] = (int32_t*)p;
   }
   *ptr = g_scratch_ptr[dev];
   *bytes = kNoAllocInts * 4;
+  *split = g_split_ptr[dev];
+  *split_bytes = kNoAllocSplitInts * 4;
   return hipSuccess;
 }
 
@@ -875,13 +797,6 @@ hipError_t wa_launch_attention(const WaAttnLaunch& a, hipStream_t stream) {
   if (a.head_dim == 64 && a.block == 128) return launch_t<64, 128>(a, stream);
   if (a.head_dim == 128 && a.block == 64) return launch_t<128, 64>(a, stream);
   if (a.head_dim == 64 && a.block == 64) return launch_t<64, 64>(a, stream);
-  return hipErrorInvalidValue;
-}
-
-hipError_t wa_launch_transpose_v(const void* v, void* vt, int64_t bh, int seq_len, int mb, int head_dim, int block,
-                                 hipStream_t stream) {
-  if (head_dim == 128) return launch_transpose<128>(v, vt, bh, seq_len, mb, block, stream);
-  if (head_dim == 64) return launch_transpose<64>(v, vt, bh, seq_len, mb, block, stream);
   return hipErrorInvalidValue;
 }
 

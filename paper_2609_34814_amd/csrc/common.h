@@ -50,6 +50,47 @@ __host__ __device__ inline size_t sched_state_ints(int64_t bh, int m, int n_xcd)
   return ilv_offset(bh, m, n_xcd) + 64 + (size_t)(bh > 0 ? bh : 0) * (m > 0 ? m : 0);
 }
 
+// Split rows. A launch with few rows ends when its longest row does, so a row of more than L kept
+// blocks is computed in chunks by several workgroups: each chunk leaves its unnormalised O, row
+// maxima and row sums in a float32 tile, and the workgroup that finishes a row's last chunk merges the
+// tiles in chunk order. L follows from the lists and the device alone (see split_plan), so a row is
+// split the same way in every execution order. The tiles take at most kPartBytes; L grows until
+// the chunks fit. Launches of more than kSplitMaxTokens / block rows never split: their rows are short
+// next to the launch (a row there outlasts its share of the launch only below 0.5% density).
+constexpr int kSplitMinBlocks = 8;  // shortest L
+constexpr size_t kPartBytes = (size_t)32 << 20;
+constexpr int64_t kSplitMaxTokens = (int64_t)1 << 22;
+__host__ __device__ inline size_t part_tile_floats(int block, int d) { return (size_t)block * (d + 2); }
+__host__ __device__ inline int split_cap(int64_t bh, int m, int block, int d) {
+  if (m <= kSplitMinBlocks || bh * m > kSplitMaxTokens / block) return 0;
+  const int64_t cap = (int64_t)(kPartBytes / (part_tile_floats(block, d) * 4));
+  const int64_t most = bh * m * ((m + kSplitMinBlocks - 1) / kSplitMinBlocks);
+  return (int)(most < cap ? most : cap);
+}
+// Split state: [0] chunk tasks, [1] tasks taken, [2] L; from 64 the tasks {head, row, chunk | chunks << 16,
+// the row's first tile}; then one arrival counter per tile, 64 bytes apart (atomics on one line
+// serialise; the row's first tile counts the row).
+__host__ __device__ inline size_t split_arrival(int cap, int tile) { return 64 + 4 * (size_t)cap + 16 * (size_t)tile; }
+__host__ __device__ inline size_t split_ints(int cap) { return (split_arrival(cap, cap) + 63) / 64 * 64; }
+
+// Lane moves through DPP (a few cycles, where a lane shuffle is an LDS round trip): lanes that the
+// control leaves without a source, or that the row mask excludes, take `old`.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ int dpp32(int old, int v) {
+  return __builtin_amdgcn_update_dpp(old, v, CTRL, ROW_MASK, 0xf, false);
+}
+// Inclusive prefix sum over the lanes: shifts by 1, 2, 4 and 8 within each row of 16, then the
+// broadcasts of lane 15 into rows 1 and 3 and of lane 31 into rows 2 and 3.
+__device__ __forceinline__ int lane_prefix_sum(int x) {
+  x += dpp32<0x111, 0xf>(0, x);  // row_shr:1
+  x += dpp32<0x112, 0xf>(0, x);  // row_shr:2
+  x += dpp32<0x114, 0xf>(0, x);  // row_shr:4
+  x += dpp32<0x118, 0xf>(0, x);  // row_shr:8
+  x += dpp32<0x142, 0xa>(0, x);  // row_bcast:15
+  x += dpp32<0x143, 0xc>(0, x);  // row_bcast:31
+  return x;
+}
+
 }  // namespace wa
 
 // Launch helpers (implemented in the .hip sources, called by the ABI layer).
@@ -61,6 +102,9 @@ struct WaAttnLaunch {
                      // workspace copy that the launch writes from v
   int32_t* sched;    // workspace: sched_state_ints(bh, mb, n_xcd) int32 (counters at [0, n_xcd), prefix
                      // tables at 64, the tail order table at tail_offset(bh, n_xcd))
+  int32_t* split;    // workspace: split_ints(split_cap) int32, then the tiles
+  float* part;       // workspace: split_cap tiles of part_tile_floats(block, head_dim)
+  int32_t split_cap;
   const int32_t* row_ptr;
   const int32_t* col_idx;
   const int32_t* perm;
@@ -79,8 +123,12 @@ struct WaAttnLaunch {
 };
 
 hipError_t wa_launch_attention(const WaAttnLaunch& a, hipStream_t stream);
-// device address and size of the calling device's static scheduler scratch (looked up on first use)
-hipError_t wa_noalloc_scratch(int32_t** ptr, size_t* bytes);
+// Order tables, split plan, cleared status word and, with a.v, the transposed copy of V, in one launch.
+// grid: workgroups of the tail-order rule; slots: workgroups of the attention kernel the chip holds.
+hipError_t wa_launch_attn_prep(const WaAttnLaunch& a, int grid, int slots, hipStream_t stream);
+// device addresses and sizes of the calling device's static scheduler scratch and split-row scratch
+// (looked up on first use)
+hipError_t wa_noalloc_scratch(int32_t** ptr, size_t* bytes, int32_t** split, size_t* split_bytes);
 hipError_t wa_launch_transpose_v(const void* v, void* vt, int64_t bh, int seq_len, int mb, int head_dim, int block,
                                  hipStream_t stream);
 hipError_t wa_attention_occupancy(int head_dim, int block, int* wgs_per_cu);

@@ -1,0 +1,101 @@
+"""Rows computed in chunks by several workgroups (launches whose longest row would outlast the rest): the
+edges of the split rule against the oracle, for every head_dim and block."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+from oracle import attention as A   # noqa: E402
+from tests.gpu_util import bf16_dev, compare_blocks, dev_f64, u8_dev   # noqa: E402
+from workloads.gen import custom, make_qkv   # noqa: E402
+
+MIN_L = 8    # the shortest L: on launches this small, rows of more kept blocks are split
+
+
+def _mask(heads, mb, rng):
+    """Row lengths around multiples of L, a full row (it holds the ragged last block), an empty row, the
+    last block alone, and the diagonal elsewhere."""
+    m = np.zeros((1, heads, mb, mb), dtype=np.uint8)
+    for h in range(heads):
+        m[0, h] = np.eye(mb, dtype=np.uint8)
+        for row, n in ((1, MIN_L - 1), (2, MIN_L), (3, MIN_L + 1), (4, 2 * MIN_L), (5, 2 * MIN_L + 1), (6, mb)):
+            m[0, h, row] = 0
+            m[0, h, row, np.sort(rng.permutation(mb)[:n])] = 1
+        m[0, h, 7] = 0
+        m[0, h, 8] = 0
+        m[0, h, 8, mb - 1] = 1
+    return m
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("block", [64, 128])
+@pytest.mark.parametrize("scale_k", [1, 32])
+def test_split_rows_vs_oracle(d, block, scale_k):
+    """scale_k = 32: K of the upper blocks scaled, so that chunks recompute against their exact maximum and
+    chunks of one row have maxima far apart."""
+    import paper_2609_34814_amd as W
+    mb, heads = 41, 2
+    wl = custom("split", heads=heads, head_dim=d, block=block, grid=(1, 1, mb * block), seq_len=mb * block - 7, seed=21)
+    rng = np.random.default_rng(d + block)
+    mask = _mask(heads, mb, rng)
+    q, k, v = make_qkv(wl)
+    kd = bf16_dev(k).float()
+    kd[:, :, mb // 2 * block:] *= scale_k      # exact: a power of two
+    kd = kd.to(torch.bfloat16)
+    k_bits = kd.view(torch.int16).cpu().numpy().view(np.uint16)
+    qd, vd, md = bf16_dev(q), bf16_dev(v), u8_dev(mask)
+    o, lse = W.sparse_attn(qd, kd, vd, md, block=block, return_lse=True)
+    ref_o, ref_lse = A.block_sparse_attention(q, k_bits, v, mask, block)
+    ref = {}
+    for h in range(heads):
+        for i in range(mb):
+            lo, hi = A.block_token_range(i, block, wl.seq_len)
+            ref[(0, h, i)] = (ref_o[0, h, lo:hi], ref_lse[0, h, lo:hi])
+    st = compare_blocks(dev_f64(o), ref, block, wl.seq_len, lse.cpu().numpy().astype(np.float64))
+    print("split", d, block, scale_k, st)
+    # bf16 probabilities and output: 2 * 2^-9 relative each; one key dominates short rows, so the
+    # absolute bar scales with max|V|
+    assert st["max_abs"] <= 4 * 2.0 ** -9 * float(np.abs(A.bf16_to_f64(v)).max()), st
+    assert st["rel_rms"] <= 1e-2 and st["lse"] <= 1e-3, st
+
+    # the split follows from the lists alone: any order, queue count and entry point gives the same bytes
+    rp, ci = W.compact_mask(md, seq_len=wl.seq_len, block=block, head_dim=d)
+    vt = W.transpose_v(vd, block=block)
+    perm = torch.from_numpy(np.stack([rng.permutation(mb) for _ in range(heads)])[None].astype(np.int32)).cuda()
+    for p, nx, order in ((perm, 8, "in-order"), (perm, 1, "interleaved"), (None, 64, "in-order")):
+        o2, l2 = W.sparse_attn_vt(qd, kd, vt, rp, ci, p, block=block, n_xcd=nx, head_order=order, return_lse=True)
+        assert torch.equal(o.view(torch.int16), o2.view(torch.int16)) and torch.equal(lse, l2)
+        out, l3 = torch.full_like(o, float("nan")), torch.full_like(lse, float("nan"))
+        W.sparse_attn_vt_noalloc(qd, kd, vt, rp, ci, p, block=block, n_xcd=nx, head_order=order, out=out, lse=l3)
+        assert torch.equal(o.view(torch.int16), out.view(torch.int16)) and torch.equal(lse, l3)
+
+    # a split row that no slot names keeps its old contents, and an invalid index in a chunk is reported
+    bad = torch.arange(mb, dtype=torch.int32, device="cuda").repeat(1, heads, 1).contiguous()
+    bad[0, 0, 6] = mb
+    ci2 = ci.clone()
+    ci2[mb * mb + int(rp[0, 1, 7].item()) - 1] = -3
+    status = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+    out = torch.full_like(o, float("nan"))
+    W.sparse_attn_vt(qd, kd, vt, rp, ci2, bad, block=block, out=out, status=status)
+    lo, hi = A.block_token_range(6, block, wl.seq_len)
+    assert int(status.item()) == 3
+    assert bool(torch.isnan(out[0, 0, lo:hi].float()).all())
+    out[0, 0, lo:hi] = o[0, 0, lo:hi]
+    out[0, 1, lo:hi] = o[0, 1, lo:hi]
+    assert torch.equal(o.view(torch.int16), out.view(torch.int16))
+
+
+def test_split_rows_up_to_the_tile_limit():
+    """More chunks than tiles: L grows until the chunks fit; 300 rows of 64 full blocks (d 128)."""
+    import paper_2609_34814_amd as W
+    mb, heads, d, block = 64, 5, 128, 128
+    wl = custom("split-limit", heads=heads, head_dim=d, block=block, grid=(1, 1, mb * block), seed=22)
+    mask = np.ones((1, heads, mb, mb), dtype=np.uint8)
+    q, k, v = make_qkv(wl)
+    o, lse = W.sparse_attn(bf16_dev(q), bf16_dev(k), bf16_dev(v), u8_dev(mask), block=block, return_lse=True)
+    picks = [(0, h, i) for h in range(heads) for i in (0, 17, mb - 1)]
+    ref = A.block_sparse_attention_rows(q, k, v, mask, block, picks)
+    st = compare_blocks(dev_f64(o), ref, block, wl.seq_len, lse.cpu().numpy().astype(np.float64))
+    assert st["max_abs"] <= 1e-2 and st["rel_rms"] <= 1e-2 and st["lse"] <= 1e-3, st
