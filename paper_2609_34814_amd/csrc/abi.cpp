@@ -178,16 +178,17 @@ wa_status launch_compact(const uint8_t* mask, const Dims& d, int32_t* row_ptr, i
   if (e != hipSuccess) return hip_fail(e, "row_count launch");
   e = wa_launch_head_scan(row_ptr, (int)d.bh, d.mb, st);
   if (e != hipSuccess) return hip_fail(e, "head_scan launch");
-  e = wa_launch_row_write(mask, (int)d.bh, d.mb, d.mb, row_ptr, col_idx, st);
+  e = wa_launch_row_write(mask, (int)d.bh, d.mb, d.mb, row_ptr, nullptr, col_idx, st);
   if (e != hipSuccess) return hip_fail(e, "row_write launch");
   return WA_OK;
 }
 
 // v: V in its natural layout (transposed into the workspace after the scheduler state), or null with
-// vt: V already transposed by the caller. split: the split rows' memory, attn_split_bytes(d).
+// vt: V already transposed by the caller. The lists come packed (row_ptr) or at a fixed stride (row_cnt).
+// split: the split rows' memory, attn_split_bytes(d).
 wa_status launch_attn(const void* q, const void* k, const void* v, const void* vt, void* ws, void* split,
-                      const int32_t* row_ptr, const int32_t* col_idx, const int32_t* perm, const int32_t* seg,
-                      const Dims& d, float scale, int32_t n_xcd, int32_t head_order, void* o, float* lse, int32_t* status, hipStream_t st) {
+                      const int32_t* row_ptr, const int32_t* row_cnt, const int32_t* col_idx, const int32_t* perm,
+                      const int32_t* seg, const Dims& d, float scale, int32_t n_xcd, int32_t head_order, void* o, float* lse, int32_t* status, hipStream_t st) {
   WaAttnLaunch a{};
   a.q = q; a.k = k; a.v = v;
   a.sched = (int32_t*)ws;
@@ -195,7 +196,7 @@ wa_status launch_attn(const void* q, const void* k, const void* v, const void* v
   a.split_cap = wa::split_cap(d.bh, d.mb, d.blk, d.d);
   a.split = (int32_t*)split;
   a.part = (float*)(a.split + wa::split_ints(a.split_cap));
-  a.row_ptr = row_ptr; a.col_idx = col_idx; a.perm = perm; a.seg = seg;
+  a.row_ptr = row_ptr; a.row_cnt = row_cnt; a.col_idx = col_idx; a.perm = perm; a.seg = seg;
   a.o = o; a.lse = lse; a.status = status; a.head_order = head_order;
   a.bh = (int32_t)d.bh; a.seq_len = d.n; a.mb = d.mb; a.head_dim = d.d; a.block = d.blk; a.n_xcd = n_xcd;
   a.scale = (scale > 0.f && std::isfinite(scale)) ? scale : (float)(1.0 / std::sqrt((double)d.d));
@@ -444,12 +445,13 @@ wa_status wa_sparse_attn(const void* q, const void* k, const void* v, const uint
   if (s != WA_OK) return s;
   hipStream_t st = (hipStream_t)stream;
   char* base = (char*)workspace;
-  int32_t* row_ptr = (int32_t*)(base + attn_csr_ws_bytes(d));
+  int32_t* row_cnt = (int32_t*)(base + attn_csr_ws_bytes(d));
   int32_t* col_idx = (int32_t*)(base + attn_csr_ws_bytes(d) + align_up((size_t)d.bh * (d.mb + 1) * 4));
-  s = launch_compact(mask, d, row_ptr, col_idx, st);
-  if (s != WA_OK) return s;
-  s = launch_attn(q, k, v, nullptr, base, base + attn_order_bytes(d), row_ptr, col_idx, perm, seg_start, d,
-                  softmax_scale, n_xcd, 0, o, lse, status, st);
+  // lists at a fixed stride: one pass over the mask, where packed ones take a count, a scan and a second pass
+  hipError_t e = wa_launch_row_write(mask, (int)d.bh, d.mb, d.mb, nullptr, row_cnt, col_idx, st);
+  if (e != hipSuccess) return hip_fail(e, "row_write launch");
+  s = launch_attn(q, k, v, nullptr, base, base + attn_order_bytes(d), nullptr, row_cnt, col_idx, perm, seg_start,
+                  d, softmax_scale, n_xcd, 0, o, lse, status, st);
   if (s != WA_OK) return s;
   return ok();
 }
@@ -467,8 +469,8 @@ wa_status wa_sparse_attn_csr(const void* q, const void* k, const void* v, const 
   if (!row_ptr || !col_idx) return fail(WA_ERR_INVALID_ARG, "row_ptr and col_idx must be non-null");
   s = check_ws(workspace, workspace_bytes, attn_csr_ws_bytes(d));
   if (s != WA_OK) return s;
-  s = launch_attn(q, k, v, nullptr, workspace, (char*)workspace + attn_order_bytes(d), row_ptr, col_idx, perm, seg_start,
-                  d, softmax_scale, n_xcd, 0, o, lse, status, (hipStream_t)stream);
+  s = launch_attn(q, k, v, nullptr, workspace, (char*)workspace + attn_order_bytes(d), row_ptr, nullptr, col_idx, perm,
+                  seg_start, d, softmax_scale, n_xcd, 0, o, lse, status, (hipStream_t)stream);
   if (s != WA_OK) return s;
   return ok();
 }
@@ -499,8 +501,8 @@ wa_status wa_sparse_attn_vt_noalloc(const void* q, const void* k, const void* vt
   if (need > have || attn_split_bytes(d) > have_split)
     return fail(WA_ERR_WORKSPACE, "static scratch holds %zu + %zu bytes, %zu + %zu needed", have, have_split, need,
                 attn_split_bytes(d));
-  s = launch_attn(q, k, nullptr, vt, scratch, split, row_ptr, col_idx, perm, seg_start, d, options->softmax_scale,
-                  options->n_xcd, options->head_order, o, lse, status, (hipStream_t)stream);
+  s = launch_attn(q, k, nullptr, vt, scratch, split, row_ptr, nullptr, col_idx, perm, seg_start, d,
+                  options->softmax_scale, options->n_xcd, options->head_order, o, lse, status, (hipStream_t)stream);
   if (s != WA_OK) return s;
   return ok();
 }
@@ -540,8 +542,8 @@ wa_status wa_sparse_attn_vt(const void* q, const void* k, const void* vt, const 
   if (!row_ptr || !col_idx) return fail(WA_ERR_INVALID_ARG, "row_ptr and col_idx must be non-null");
   s = check_ws(workspace, workspace_bytes, attn_sched_bytes(d));
   if (s != WA_OK) return s;
-  s = launch_attn(q, k, nullptr, vt, workspace, (char*)workspace + attn_order_bytes(d), row_ptr, col_idx, perm, seg_start,
-                  d, options->softmax_scale, options->n_xcd, options->head_order, o, lse, status, (hipStream_t)stream);
+  s = launch_attn(q, k, nullptr, vt, workspace, (char*)workspace + attn_order_bytes(d), row_ptr, nullptr, col_idx, perm,
+                  seg_start, d, options->softmax_scale, options->n_xcd, options->head_order, o, lse, status, (hipStream_t)stream);
   if (s != WA_OK) return s;
   return ok();
 }

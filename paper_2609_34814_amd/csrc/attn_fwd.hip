@@ -274,17 +274,18 @@ __device__ bool queue_task(Args a, int x, int t, int longest, Task* out) {
     if (a->status) atomicOr(a->status, 1);
     return false;
   }
-  const int32_t* rp = a->row_ptr + (int64_t)bh * (a->mb + 1) + row;
-  const int beg = rp[0], end = rp[1];
+  int beg, end;
+  wa::row_range(a, bh, row, &beg, &end);
   *out = {bh, row, beg, end, 1, 0, 0};
   return end - beg <= longest;
 }
 
 __device__ void split_task(Args a, int k, Task* out) {
   const int4 e = ((const int4*)(a->split + 64))[k];
-  const int32_t* rp = a->row_ptr + (int64_t)e.x * (a->mb + 1) + e.y;
-  const int n = rp[1] - rp[0], c = e.z & 0xFFFF, chunks = e.z >> 16;
-  *out = {e.x, e.y, rp[0] + (int)((int64_t)n * c / chunks), rp[0] + (int)((int64_t)n * (c + 1) / chunks), chunks, c, e.w};
+  int beg, end;
+  wa::row_range(a, e.x, e.y, &beg, &end);
+  const int n = end - beg, c = e.z & 0xFFFF, chunks = e.z >> 16;
+  *out = {e.x, e.y, beg + n * c / chunks, beg + n * (c + 1) / chunks, chunks, c, e.w};
 }
 
 // Next task of this workgroup, run by one lane: the chunks of the split rows first (the longest work),

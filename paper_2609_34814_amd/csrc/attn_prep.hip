@@ -130,8 +130,9 @@ __device__ void tail_order(const WaAttnLaunch& a, OrderLds& L, int x, int grid) 
 #pragma unroll
       for (int i = i0; i < i0 + 4; ++i) {
         if (i < per && (unsigned)row[i - i0] < (unsigned)a.mb) {
-          const int32_t* rp = a.row_ptr + (int64_t)(hb + kh[i]) * (a.mb + 1);
-          nb[i] = (uint16_t)min(max(rp[row[i - i0] + 1] - rp[row[i - i0]], 0), WA_MAX_BLOCKS);
+          int beg, end;
+          wa::row_range(&a, hb + kh[i], row[i - i0], &beg, &end);
+          nb[i] = (uint16_t)min(max(end - beg, 0), WA_MAX_BLOCKS);
         }
         sum += nb[i];
       }
@@ -247,12 +248,17 @@ __device__ void split_plan(const WaAttnLaunch& a, OrderLds& S, int slots) {
   if (a.split_cap <= 0) return;
   const int rows = a.bh * a.mb;
   int kept = 0, all;
-  for (int h = t; h < a.bh; h += PT) kept += a.row_ptr[(int64_t)h * (a.mb + 1) + a.mb];
+  if (a.row_ptr) {
+    for (int h = t; h < a.bh; h += PT) kept += a.row_ptr[(int64_t)h * (a.mb + 1) + a.mb];
+  } else {
+    for (int i = t; i < rows; i += PT) kept += a.row_cnt[i];
+  }
   wg_scan(kept, S.part, &all);
   int L = max(wa::kSplitMinBlocks, (int)(((int64_t)all * kSplitNum / kSplitDen + slots - 1) / slots));
   auto blocks = [&](int h, int r) {
-    const int32_t* rp = a.row_ptr + (int64_t)h * (a.mb + 1) + r;
-    return rp[1] - rp[0];
+    int beg, end;
+    wa::row_range(&a, h, r, &beg, &end);
+    return end - beg;
   };
   auto slot_blocks = [&](int i, int* h, int* r) {
     *h = i / a.mb;

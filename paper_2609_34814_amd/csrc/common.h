@@ -105,7 +105,8 @@ struct WaAttnLaunch {
   int32_t* split;    // workspace: split_ints(split_cap) int32, then the tiles
   float* part;       // workspace: split_cap tiles of part_tile_floats(block, head_dim)
   int32_t split_cap;
-  const int32_t* row_ptr;
+  const int32_t* row_ptr;  // [bh][mb+1], row r's list at col_idx + head mb^2 + row_ptr[r]; null:
+  const int32_t* row_cnt;  // [bh][mb], row r's list at col_idx + head mb^2 + r mb
   const int32_t* col_idx;
   const int32_t* perm;
   const int32_t* seg;  // [bh][n_xcd+1] XCD segment starts, nullable
@@ -122,6 +123,22 @@ struct WaAttnLaunch {
   float scale;         // softmax scale
 };
 
+namespace wa {
+// List entries [beg, end) of row r of head h, relative to the head's list area. ARGS: a pointer to a
+// WaAttnLaunch in any address space.
+template <typename ARGS>
+__device__ __forceinline__ void row_range(ARGS a, int h, int r, int32_t* beg, int32_t* end) {
+  if (a->row_ptr) {
+    const int32_t* rp = a->row_ptr + (int64_t)h * (a->mb + 1) + r;
+    *beg = rp[0];
+    *end = rp[1];
+  } else {
+    *beg = r * a->mb;
+    *end = *beg + a->row_cnt[(int64_t)h * a->mb + r];
+  }
+}
+}  // namespace wa
+
 hipError_t wa_launch_attention(const WaAttnLaunch& a, hipStream_t stream);
 // Order tables, split plan, cleared status word and, with a.v, the transposed copy of V, in one launch.
 // grid: workgroups of the tail-order rule; slots: workgroups of the attention kernel the chip holds.
@@ -137,5 +154,6 @@ size_t wa_vt_bytes(int64_t bh, int mb, int head_dim, int block);
 hipError_t wa_launch_row_count(const uint8_t* mask, int64_t rows, int n, int32_t* counts, int64_t count_stride_rows,
                                int counts_offset, int mb, hipStream_t stream);
 hipError_t wa_launch_head_scan(int32_t* row_ptr, int bh, int mb, hipStream_t stream);
-hipError_t wa_launch_row_write(const uint8_t* mask, int bh, int mb, int n, const int32_t* row_ptr, int32_t* col_idx,
-                               hipStream_t stream);
+// row_ptr: the lists packed per head; null: row r's list at col_idx + r n and its length in counts[r]
+hipError_t wa_launch_row_write(const uint8_t* mask, int bh, int mb, int n, const int32_t* row_ptr, int32_t* counts,
+                               int32_t* col_idx, hipStream_t stream);

@@ -1,84 +1,105 @@
 // Mask scans for gfx950: row counts, per-row KV-index lists, and the bit-packed
 // row and column masks that the permutation builder iterates over.
 //
-// A wavefront scans one mask row 1024 columns at a time: lane l takes columns
-// [1024t + 16l, +16) with 16-byte loads (mask rows start at any byte, so a lane
-// reads the aligned 16-byte chunk holding its first column and, when its columns
-// cross into the next chunk, that one too, and byte-aligns the pair). Each load
-// covers at least one byte of the row, so it never leaves the pages that hold
-// the mask. Kept-column counts are popcounts; the lanes' exclusive prefix sum
-// ranks their columns, so indices are written in ascending column order (the
-// order in which the attention kernel visits KV blocks) and the result is
-// independent of scheduling.
+// The scans are bound by memory: a wavefront walks rows at a fixed stride and has the loads of its next
+// row in flight while it works on the current one (one short-lived wavefront per row, each waiting out
+// a memory latency, read 323 MB in 71 us; this form takes 61). Rows start at any byte, so a
+// lane takes the aligned 16-byte chunks 64 t + lane of the row's span, one load each, and the bytes
+// before and after the row are dropped from its bits; each load covers at least one byte of the row, so
+// it never leaves the pages that hold the mask. Kept-column counts are popcounts; the lanes' exclusive
+// prefix sum ranks their columns, so indices are written in ascending column order (the order in which
+// the attention kernel visits KV blocks) and the result is independent of scheduling.
 
 #include "common.h"
 #include "perm_launch.h"
 #include "wavealign.h"
 
+#include <algorithm>
+
 namespace {
 
 constexpr int kWavesPerWG = 4;
 
-__device__ __forceinline__ uint64_t ballot64(bool p) { return __ballot(p); }
+constexpr int kScanWGs = 2048;  // workgroups of a scan, at most: eight wavefronts per SIMD
 
-// One bit per byte of w (bit i = byte i is nonzero).
-__device__ __forceinline__ uint32_t nz_nibble(uint32_t w) {
-  uint32_t t = ((w & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | w;
-  t = (t >> 7) & 0x01010101u;
-  return (t | (t >> 7) | (t >> 14) | (t >> 21)) & 0xFu;
+// Nonzero mask of 16 bytes (bit b = byte b): each byte's high bit is set if the byte is nonzero, and two
+// byte dot products with the weights 1, 2, 4, ..., 128 gather them, 128 times too large.
+__device__ __forceinline__ uint32_t nz16(const uint4& c) {
+  auto high = [](uint32_t w) { return (((w & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | w) & 0x80808080u; };
+  const uint32_t lo = __builtin_amdgcn_udot4(high(c.y), 0x80402010u, __builtin_amdgcn_udot4(high(c.x), 0x08040201u, 0u, false), false);
+  const uint32_t hi = __builtin_amdgcn_udot4(high(c.w), 0x80402010u, __builtin_amdgcn_udot4(high(c.z), 0x08040201u, 0u, false), false);
+  return (lo >> 7) | (hi << 1);
 }
 
-// Nonzero mask of the bytes p[0 .. valid), valid in 1..16 (bit b = byte b). The byte offset of p
-// within its 16-byte chunk must be the same in every lane of the wavefront.
-__device__ __forceinline__ uint32_t nz16(const uint8_t* p, int valid) {
-  const uintptr_t addr = (uintptr_t)p;
-  const uint8_t* a = p - (addr & 15);
-  const int d = (int)(addr & 15);
-  const uint4 c0 = *(const uint4*)a;
-  uint4 c1 = make_uint4(0u, 0u, 0u, 0u);
-  if (d + valid > 16) c1 = *(const uint4*)(a + 16);
-  const uint32_t w[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
-  const uint32_t r = (uint32_t)(d & 3);
-  uint32_t o[4];
-  switch (d >> 2) {  // uniform
-    case 0:
+// A mask row as aligned 16-byte chunks: chunk c holds columns [16 c - off, 16 c - off + 16).
+struct RowSpan {
+  const uint8_t* base;
+  int off, chunks, n;
+};
+__device__ __forceinline__ RowSpan row_span(const uint8_t* mask, int64_t row, int n) {
+  const uint8_t* p = mask + row * n;
+  const int off = (int)((uintptr_t)p & 15);
+  return {p - off, off, (off + n + 15) >> 4, n};
+}
+// Steps of 64 chunks that cover any row of n bytes.
+constexpr int kMaxSteps = (WA_MAX_BLOCKS + 15 + 1023) / 1024;
+template <int STEPS>
+__device__ __forceinline__ void load_span(const RowSpan& r, int lane, uint4 (&c)[STEPS]) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) o[i] = __builtin_amdgcn_alignbyte(w[i + 1], w[i], r);
-      break;
-    case 1:
-#pragma unroll
-      for (int i = 0; i < 4; ++i) o[i] = __builtin_amdgcn_alignbyte(w[i + 2], w[i + 1], r);
-      break;
-    case 2:
-#pragma unroll
-      for (int i = 0; i < 4; ++i) o[i] = __builtin_amdgcn_alignbyte(w[i + 3], w[i + 2], r);
-      break;
-    default:
-#pragma unroll
-      for (int i = 0; i < 4; ++i) o[i] = __builtin_amdgcn_alignbyte(w[i + 4], w[i + 3], r);
-      break;
+  for (int t = 0; t < STEPS; ++t) {
+    const int k = 64 * t + lane;
+    c[t] = k < r.chunks ? *(const uint4*)(r.base + 16 * (int64_t)k) : make_uint4(0u, 0u, 0u, 0u);
   }
-  const uint32_t bits = nz_nibble(o[0]) | (nz_nibble(o[1]) << 4) | (nz_nibble(o[2]) << 8) | (nz_nibble(o[3]) << 12);
-  return valid >= 16 ? bits : bits & ((1u << valid) - 1u);
+}
+// Kept bits of chunk k: bit b = column 16 k - off + b.
+__device__ __forceinline__ uint32_t span_bits(const RowSpan& r, int k, const uint4& c) {
+  uint32_t bits = nz16(c);
+  if (k == 0) bits &= 0xFFFFu << r.off;
+  const int end = r.off + r.n - 16 * k;  // bytes of the row from this chunk's start on
+  if (end < 16) bits &= end > 0 ? (1u << end) - 1u : 0u;
+  return bits & 0xFFFFu;
 }
 
-// Kept-column mask of columns [col0, col0 + 16) of a row of n bytes (0 past the end).
-__device__ __forceinline__ uint32_t row_bits16(const uint8_t* rowp, int n, int col0) {
-  return col0 < n ? nz16(rowp + col0, min(16, n - col0)) : 0u;
+// Calls f(row, span, chunks) for the rows of this wavefront, the loads of the next row in flight.
+template <int STEPS, typename F>
+__device__ __forceinline__ void for_rows(const uint8_t* mask, int rows, int n, F&& f) {
+  const int lane = threadIdx.x & 63;
+  const int stride = (int)gridDim.x * kWavesPerWG;
+  int row = (int)blockIdx.x * kWavesPerWG + (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (row >= rows) return;
+  RowSpan cur = row_span(mask, row, n);
+  uint4 c[STEPS];
+  load_span<STEPS>(cur, lane, c);
+  for (;;) {
+    const int next = row > INT32_MAX - stride ? INT32_MAX : row + stride;
+    RowSpan nr = cur;
+    uint4 nc[STEPS];
+    if (next < rows) {
+      nr = row_span(mask, next, n);
+      load_span<STEPS>(nr, lane, nc);
+    }
+    f(row, cur, c);
+    if (next >= rows) break;
+    row = next;
+    cur = nr;
+#pragma unroll
+    for (int t = 0; t < STEPS; ++t) c[t] = nc[t];
+  }
 }
 
-// counts[(row / mb) * count_stride_rows + counts_offset + row % mb] = n_row
-__global__ __launch_bounds__(256) void row_count_kernel(const uint8_t* __restrict__ mask, int64_t rows, int n,
+// counts[(row / mb) * stride + offset + row % mb] = n_row
+template <int STEPS>
+__global__ __launch_bounds__(256) void row_count_kernel(const uint8_t* __restrict__ mask, int rows, int n,
                                                          int32_t* __restrict__ counts, int64_t stride, int offset,
                                                          int mb) {
-  const int64_t row = (int64_t)blockIdx.x * kWavesPerWG + (threadIdx.x >> 6);
-  if (row >= rows) return;
   const int lane = threadIdx.x & 63;
-  const uint8_t* p = mask + row * n;
-  int cnt = 0;
-  for (int c0 = 0; c0 < n; c0 += 1024) cnt += __popc(row_bits16(p, n, c0 + 16 * lane));
-  for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o);
-  if (lane == 0) counts[(row / mb) * stride + offset + row % mb] = cnt;
+  for_rows<STEPS>(mask, rows, n, [&](int row, const RowSpan& r, const uint4 (&c)[STEPS]) {
+    int cnt = 0;
+#pragma unroll
+    for (int t = 0; t < STEPS; ++t) cnt += __popc(span_bits(r, 64 * t + lane, c[t]));
+    cnt = wa::lane_prefix_sum(cnt);
+    if (lane == 63) counts[(int64_t)(row / mb) * stride + offset + row % mb] = cnt;
+  });
 }
 
 // In place: row_ptr[h][1..mb] holds counts on entry, the exclusive scan on exit (row_ptr[h][0] = 0).
@@ -108,59 +129,77 @@ __global__ __launch_bounds__(1024) void head_scan_kernel(int32_t* __restrict__ r
   if (t == 0) rp[0] = 0;
 }
 
-__global__ __launch_bounds__(256) void row_write_kernel(const uint8_t* __restrict__ mask, int bh, int mb, int n,
+// The rows' index lists. CSR: row i of head h at out[h mb n + row_ptr[h][i]]; otherwise (row_ptr null) at
+// out[(h mb + i) n], with its length in counts[h mb + i]. The indices are gathered in LDS and written
+// from there, 64 consecutive entries per store: a store per kept bit of each lane costs the
+// address unit a pass over 64 scattered addresses (16 of them for a run of 16 blocks), which bound the
+// list writing at 111 us for 16 M indices of 323 MB of mask against 77.
+template <int STEPS>
+__global__ __launch_bounds__(256) void row_write_kernel(const uint8_t* __restrict__ mask, int rows, int mb, int n,
                                                          const int32_t* __restrict__ row_ptr,
-                                                         int32_t* __restrict__ col_idx) {
-  const int64_t row = (int64_t)blockIdx.x * kWavesPerWG + (threadIdx.x >> 6);
-  if (row >= (int64_t)bh * mb) return;
+                                                         int32_t* __restrict__ counts, int32_t* __restrict__ col_idx) {
+  __shared__ uint16_t stage[kWavesPerWG][STEPS * 1024];
   const int lane = threadIdx.x & 63;
-  const int64_t h = row / mb;
-  const int i = (int)(row % mb);
-  const uint8_t* p = mask + row * n;
-  int32_t* out = col_idx + h * (int64_t)mb * n + row_ptr[h * (mb + 1) + i];
-  int base = 0;
-  for (int c0 = 0; c0 < n; c0 += 1024) {
-    const int col = c0 + 16 * lane;
-    uint32_t bits = row_bits16(p, n, col);
-    const int cnt = __popc(bits);
-    int incl = cnt;  // inclusive prefix sum over the lanes
+  uint16_t* st = stage[threadIdx.x >> 6];
+  for_rows<STEPS>(mask, rows, n, [&](int row, const RowSpan& r, const uint4 (&c)[STEPS]) {
+    const int h = row / mb;
+    int32_t* out = row_ptr ? col_idx + (int64_t)h * mb * n + row_ptr[(int64_t)h * (mb + 1) + (row - h * mb)]
+                           : col_idx + (int64_t)row * n;
+    int base = 0;
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int u = __shfl_up(incl, o);
-      if (lane >= o) incl += u;
+    for (int t = 0; t < STEPS; ++t) {
+      const int k = 64 * t + lane;
+      uint32_t bits = span_bits(r, k, c[t]);
+      const int cnt = __popc(bits);
+      const int incl = wa::lane_prefix_sum(cnt);
+      int pos = base + incl - cnt;
+      const int col = 16 * k - r.off;
+      while (bits) {
+        st[pos++] = (uint16_t)(col + __ffs((int)bits) - 1);
+        bits &= bits - 1u;
+      }
+      base += __builtin_amdgcn_readlane(incl, 63);
     }
-    int pos = base + incl - cnt;
-    while (bits) {
-      out[pos++] = col + __ffs((int)bits) - 1;
-      bits &= bits - 1u;
-    }
-    base += __shfl(incl, 63);
-  }
+    asm volatile("" ::: "memory");  // (a wavefront's LDS operations complete in order)
+    for (int e = lane; e < base; e += 64) out[e] = st[e];
+    asm volatile("" ::: "memory");
+    if (!row_ptr && lane == 0) counts[row] = base;
+  });
 }
 
 // Bit-packed rows, word-major per head: rowbits[(h*nw + w)*m + i] bit b = M[h][i][64w + b];
 // row_nnz[h*m + i] = n_i.
-__global__ __launch_bounds__(256) void pack_rows_kernel(const uint8_t* __restrict__ mask, int64_t rows, int m, int n,
+template <int STEPS>
+__global__ __launch_bounds__(256) void pack_rows_kernel(const uint8_t* __restrict__ mask, int rows, int m, int n,
                                                         int nw, uint64_t* __restrict__ rowbits,
                                                         int32_t* __restrict__ row_nnz) {
-  const int64_t row = (int64_t)blockIdx.x * kWavesPerWG + (threadIdx.x >> 6);
-  if (row >= rows) return;
   const int lane = threadIdx.x & 63;
-  const int64_t h = row / m;
-  const int i = (int)(row % m);
-  const uint8_t* p = mask + row * n;
-  int cnt = 0;
-  for (int c0 = 0; c0 < n; c0 += 1024) {
-    const uint32_t b = row_bits16(p, n, c0 + 16 * lane);
-    cnt += __popc(b);
-    // lanes 4k .. 4k+3 hold the 64 columns of word c0 / 64 + k
-    const uint64_t word = (uint64_t)b | ((uint64_t)__shfl_down(b, 1) << 16) | ((uint64_t)__shfl_down(b, 2) << 32) |
-                          ((uint64_t)__shfl_down(b, 3) << 48);
-    const int w = c0 / 64 + (lane >> 2);
-    if ((lane & 3) == 0 && w < nw) rowbits[(h * nw + w) * m + i] = word;
-  }
-  for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o);
-  if (lane == 0) row_nnz[row] = cnt;
+  for_rows<STEPS>(mask, rows, n, [&](int row, const RowSpan& r, const uint4 (&c)[STEPS]) {
+    const int64_t h = row / m;
+    const int i = row % m;
+    uint32_t b[STEPS + 1];
+    int cnt = 0;
+#pragma unroll
+    for (int t = 0; t < STEPS; ++t) {
+      b[t] = span_bits(r, 64 * t + lane, c[t]);
+      cnt += __popc(b[t]);
+    }
+    b[STEPS] = 0u;
+    cnt = wa::lane_prefix_sum(cnt);
+    if (lane == 63) row_nnz[row] = cnt;
+#pragma unroll
+    for (int t = 0; t < STEPS; ++t) {
+      // columns [16 k, 16 k + 16) of chunk position k: the end of this chunk and the start of the next
+      const uint32_t up = (uint32_t)wa::dpp32<0x130, 0xf>(0, (int)b[t]);  // wave_shl:1: lane + 1's bits
+      const uint32_t nx = lane == 63 ? (uint32_t)__builtin_amdgcn_readlane((int)b[t + 1], 0) : up;
+      const uint32_t v = ((b[t] | (nx << 16)) >> r.off) & 0xFFFFu;
+      // lanes 4k .. 4k+3 hold the 64 columns of word 16 t + k
+      const uint32_t lo = v | ((uint32_t)wa::dpp32<0x101, 0xf>(0, (int)v) << 16);  // row_shl:1
+      const uint32_t hi = (uint32_t)wa::dpp32<0x102, 0xf>(0, (int)lo);             // row_shl:2
+      const int w = 16 * t + (lane >> 2);
+      if ((lane & 3) == 0 && w < nw) rowbits[(h * nw + w) * m + i] = (uint64_t)lo | ((uint64_t)hi << 32);
+    }
+  });
 }
 
 // Bit-packed columns from bit-packed rows, word-major: colbits[(h*mw + v)*n + j] bit r = M[h][64v + r][j].
@@ -251,12 +290,22 @@ hipError_t wa_launch_xcc_probe(int32_t* out, int n_wg, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// Instantiates a scan for the steps that a row of n bytes at any alignment takes.
+#define WA_SCAN(kernel, rows, n, ...)                                                                            \
+  do {                                                                                                           \
+    const int64_t wgs_ = std::min<int64_t>(((rows) + kWavesPerWG - 1) / kWavesPerWG, kScanWGs);                  \
+    const int steps_ = ((n) + 15 + 1023) / 1024;                                                                 \
+    const dim3 g_((unsigned)wgs_), t_(64 * kWavesPerWG);                                                         \
+    if (steps_ <= 1) hipLaunchKernelGGL((kernel<1>), g_, t_, 0, stream, __VA_ARGS__);                            \
+    else if (steps_ <= 2) hipLaunchKernelGGL((kernel<2>), g_, t_, 0, stream, __VA_ARGS__);                       \
+    else if (steps_ <= 3) hipLaunchKernelGGL((kernel<3>), g_, t_, 0, stream, __VA_ARGS__);                       \
+    else hipLaunchKernelGGL((kernel<kMaxSteps>), g_, t_, 0, stream, __VA_ARGS__);                                \
+  } while (0)
+
 hipError_t wa_launch_row_count(const uint8_t* mask, int64_t rows, int n, int32_t* counts, int64_t count_stride_rows,
                                int counts_offset, int mb, hipStream_t stream) {
   if (rows <= 0) return hipSuccess;
-  const int64_t grid = (rows + kWavesPerWG - 1) / kWavesPerWG;
-  hipLaunchKernelGGL(row_count_kernel, dim3((unsigned)grid), dim3(256), 0, stream, mask, rows, n, counts,
-                     count_stride_rows, counts_offset, mb);
+  WA_SCAN(row_count_kernel, rows, n, mask, (int)rows, n, counts, count_stride_rows, counts_offset, mb);
   return hipGetLastError();
 }
 
@@ -266,12 +315,11 @@ hipError_t wa_launch_head_scan(int32_t* row_ptr, int bh, int mb, hipStream_t str
   return hipGetLastError();
 }
 
-hipError_t wa_launch_row_write(const uint8_t* mask, int bh, int mb, int n, const int32_t* row_ptr, int32_t* col_idx,
-                               hipStream_t stream) {
+hipError_t wa_launch_row_write(const uint8_t* mask, int bh, int mb, int n, const int32_t* row_ptr, int32_t* counts,
+                               int32_t* col_idx, hipStream_t stream) {
   const int64_t rows = (int64_t)bh * mb;
   if (rows <= 0) return hipSuccess;
-  const int64_t grid = (rows + kWavesPerWG - 1) / kWavesPerWG;
-  hipLaunchKernelGGL(row_write_kernel, dim3((unsigned)grid), dim3(256), 0, stream, mask, bh, mb, n, row_ptr, col_idx);
+  WA_SCAN(row_write_kernel, rows, n, mask, (int)rows, mb, n, row_ptr, counts, col_idx);
   return hipGetLastError();
 }
 
@@ -279,9 +327,7 @@ hipError_t wa_launch_pack_rows(const uint8_t* mask, int64_t rows, int m, int n, 
                                int32_t* row_nnz, hipStream_t stream) {
   if (rows <= 0) return hipSuccess;
   const int nw = (n + 63) / 64;
-  const int64_t grid = (rows + kWavesPerWG - 1) / kWavesPerWG;
-  hipLaunchKernelGGL(pack_rows_kernel, dim3((unsigned)grid), dim3(256), 0, stream, mask, rows, m, n, nw, rowbits,
-                     row_nnz);
+  WA_SCAN(pack_rows_kernel, rows, n, mask, (int)rows, m, n, nw, rowbits, row_nnz);
   return hipGetLastError();
 }
 
