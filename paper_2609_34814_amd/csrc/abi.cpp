@@ -89,24 +89,23 @@ ProducerWs producer_ws_layout(const Dims& d) {
 }
 
 struct PermWs {
-  size_t rowbits, colbits, row_nnz, col_cnt, head_stats, xg, ym, z, state, total;
-  int slices;
+  size_t rowbits, colbits, row_nnz, col_cnt, xg, ym, z, state, adj, stats, total;
 };
 
 PermWs perm_ws_layout(const Dims& d) {
   PermWs w{};
   const int64_t words = (d.mb + 63) / 64;
-  w.slices = wa_perm_slices(d.mb);
   size_t off = 0;
   w.rowbits = off; off = align_up(off + (size_t)d.bh * d.mb * words * 8);
   w.colbits = off; off = align_up(off + (size_t)d.bh * d.mb * words * 8);
   w.row_nnz = off; off = align_up(off + (size_t)d.bh * d.mb * 4);
   w.col_cnt = off; off = align_up(off + (size_t)d.bh * d.mb * 4);
-  w.head_stats = off; off = align_up(off + (size_t)d.bh * 6 * 8);
   w.xg = off; off = align_up(off + (size_t)d.bh * d.mb * 2 * 4);
   w.ym = off; off = align_up(off + (size_t)d.bh * d.mb * 2 * 8);
   w.z = off; off = align_up(off + (size_t)d.bh * d.mb * 2 * 8);
   w.state = off; off = align_up(off + (size_t)d.bh * sizeof(PermState));
+  w.adj = off; off = align_up(off + (size_t)d.bh * words * sizeof(int2));
+  w.stats = off; off = align_up(off + (size_t)d.bh * wa_perm_stat_runs(d.mb) * sizeof(PermStats));
   w.total = off;
   return w;
 }
@@ -119,7 +118,8 @@ void perm_ws_pointers(WaPermLaunch& a, const PermWs& L, char* base) {
   a.ym = (int64_t*)(base + L.ym);
   a.z = (int64_t*)(base + L.z);
   a.state = (PermState*)(base + L.state);
-  a.slices = L.slices;
+  a.adj = (const int2*)(base + L.adj);
+  a.stats = (PermStats*)(base + L.stats);
 }
 
 // Attention workspace: [scheduler state][split rows][V^T copy][row_ptr][col_idx]; the CSR entry point
@@ -188,7 +188,8 @@ wa_status launch_compact(const uint8_t* mask, const Dims& d, int32_t* row_ptr, i
 // split: the split rows' memory, attn_split_bytes(d).
 wa_status launch_attn(const void* q, const void* k, const void* v, const void* vt, void* ws, void* split,
                       const int32_t* row_ptr, const int32_t* row_cnt, const int32_t* col_idx, const int32_t* perm,
-                      const int32_t* seg, const Dims& d, float scale, int32_t n_xcd, int32_t head_order, void* o, float* lse, int32_t* status, hipStream_t st) {
+                      const int32_t* seg, const Dims& d, float scale, int32_t n_xcd, int32_t head_order, void* o,
+                      float* lse, int32_t* status, hipStream_t st) {
   WaAttnLaunch a{};
   a.q = q; a.k = k; a.v = v;
   a.sched = (int32_t*)ws;
@@ -208,11 +209,9 @@ wa_status launch_attn(const void* q, const void* k, const void* v, const void* v
 wa_status perm_launch_common(const uint8_t* mask, const Dims& d, const PermWs& L, char* base, hipStream_t st,
                              int32_t* row_nnz_out) {
   int32_t* row_nnz = row_nnz_out ? row_nnz_out : (int32_t*)(base + L.row_nnz);
-  hipError_t e = wa_launch_pack_rows(mask, d.bh * d.mb, d.mb, d.mb, (uint64_t*)(base + L.rowbits), row_nnz, st);
-  if (e != hipSuccess) return hip_fail(e, "pack_rows launch");
-  e = wa_launch_transpose_bits((const uint64_t*)(base + L.rowbits), (int)d.bh, d.mb, d.mb,
-                               (uint64_t*)(base + L.colbits), st);
-  if (e != hipSuccess) return hip_fail(e, "transpose_bits launch");
+  hipError_t e = wa_launch_pack(mask, (int)d.bh, d.mb, d.mb, (uint64_t*)(base + L.rowbits), (uint64_t*)(base + L.colbits),
+                                row_nnz, (int2*)(base + L.adj), st);
+  if (e != hipSuccess) return hip_fail(e, "pack launch");
   return WA_OK;
 }
 
@@ -543,7 +542,8 @@ wa_status wa_sparse_attn_vt(const void* q, const void* k, const void* vt, const 
   s = check_ws(workspace, workspace_bytes, attn_sched_bytes(d));
   if (s != WA_OK) return s;
   s = launch_attn(q, k, nullptr, vt, workspace, (char*)workspace + attn_order_bytes(d), row_ptr, nullptr, col_idx, perm,
-                  seg_start, d, options->softmax_scale, options->n_xcd, options->head_order, o, lse, status, (hipStream_t)stream);
+                  seg_start, d, options->softmax_scale, options->n_xcd, options->head_order, o, lse, status,
+                  (hipStream_t)stream);
   if (s != WA_OK) return s;
   return ok();
 }

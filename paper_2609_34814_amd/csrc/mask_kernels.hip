@@ -26,8 +26,10 @@ constexpr int kScanWGs = 2048;  // workgroups of a scan, at most: eight wavefron
 // byte dot products with the weights 1, 2, 4, ..., 128 gather them, 128 times too large.
 __device__ __forceinline__ uint32_t nz16(const uint4& c) {
   auto high = [](uint32_t w) { return (((w & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | w) & 0x80808080u; };
-  const uint32_t lo = __builtin_amdgcn_udot4(high(c.y), 0x80402010u, __builtin_amdgcn_udot4(high(c.x), 0x08040201u, 0u, false), false);
-  const uint32_t hi = __builtin_amdgcn_udot4(high(c.w), 0x80402010u, __builtin_amdgcn_udot4(high(c.z), 0x08040201u, 0u, false), false);
+  auto gather = [&](uint32_t w0, uint32_t w1) {
+    return __builtin_amdgcn_udot4(high(w1), 0x80402010u, __builtin_amdgcn_udot4(high(w0), 0x08040201u, 0u, false), false);
+  };
+  const uint32_t lo = gather(c.x, c.y), hi = gather(c.z, c.w);
   return (lo >> 7) | (hi << 1);
 }
 
@@ -167,71 +169,110 @@ __global__ __launch_bounds__(256) void row_write_kernel(const uint8_t* __restric
   });
 }
 
-// Bit-packed rows, word-major per head: rowbits[(h*nw + w)*m + i] bit b = M[h][i][64w + b];
-// row_nnz[h*m + i] = n_i.
+// The bit-packed mask of the permutation builder: one workgroup packs 64 rows of a head into words in
+// LDS and writes them in both layouts, in 512-byte runs:
+//   rows     rowbits[(h nw + w) m + i], bit b = M[h][i][64 w + b]
+//   columns  colbits[(h mw + v) n + j], bit r = M[h][64 v + r][j]
+// with row_nnz[h m + i] = n_i, and per 64-row group v the adjacent-row overlap within it,
+// adj[h mw + v] = {sum |M_i & M_i+1|, sum |M_i | M_i+1|} over its rows i and i + 1 (the pairs that straddle two
+// groups are left to the statistics). Packing row by row wrote each word by itself (8 bytes of a line
+// whose other rows other XCDs wrote) and re-read the words for the columns: 94 + 33 us for 323 MB of
+// mask against 90.
+constexpr int kPackWaves = 16;
 template <int STEPS>
-__global__ __launch_bounds__(256) void pack_rows_kernel(const uint8_t* __restrict__ mask, int rows, int m, int n,
-                                                        int nw, uint64_t* __restrict__ rowbits,
-                                                        int32_t* __restrict__ row_nnz) {
+__global__ __launch_bounds__(64 * kPackWaves, 8) void pack_kernel(const uint8_t* __restrict__ mask, int m, int n,
+                                                                  int nw, int mw, uint64_t* __restrict__ rowbits,
+                                                                  uint64_t* __restrict__ colbits,
+                                                                  int32_t* __restrict__ row_nnz,
+                                                                  int2* __restrict__ adj) {
+  constexpr int W = (16 * STEPS < WA_MAX_BLOCKS / 64 ? 16 * STEPS : WA_MAX_BLOCKS / 64) + 1;  // (+1: bank conflicts)
+  __shared__ uint64_t words[64][W];
+  __shared__ int2 part[kPackWaves];
   const int lane = threadIdx.x & 63;
-  for_rows<STEPS>(mask, rows, n, [&](int row, const RowSpan& r, const uint4 (&c)[STEPS]) {
-    const int64_t h = row / m;
-    const int i = row % m;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t h = blockIdx.x / mw;
+  const int v = (int)(blockIdx.x % mw);
+  const int r0 = 64 * v, rows = min(64, m - r0);
+  const uint8_t* base = mask + (h * m + r0) * n;
+  RowSpan cur = {};
+  uint4 c[STEPS];
+  if (wv < rows) {
+    cur = row_span(base, wv, n);
+    load_span<STEPS>(cur, lane, c);
+  }
+  for (int r = wv; r < 64; r += kPackWaves) {
+    RowSpan nr = cur;
+    uint4 nc[STEPS];
+    const int next = r + kPackWaves;
+    if (next < rows) {
+      nr = row_span(base, next, n);
+      load_span<STEPS>(nr, lane, nc);
+    }
     uint32_t b[STEPS + 1];
     int cnt = 0;
 #pragma unroll
     for (int t = 0; t < STEPS; ++t) {
-      b[t] = span_bits(r, 64 * t + lane, c[t]);
+      b[t] = r < rows ? span_bits(cur, 64 * t + lane, c[t]) : 0u;
       cnt += __popc(b[t]);
     }
     b[STEPS] = 0u;
     cnt = wa::lane_prefix_sum(cnt);
-    if (lane == 63) row_nnz[row] = cnt;
+    if (lane == 63 && r < rows) row_nnz[h * m + r0 + r] = cnt;
 #pragma unroll
     for (int t = 0; t < STEPS; ++t) {
       // columns [16 k, 16 k + 16) of chunk position k: the end of this chunk and the start of the next
       const uint32_t up = (uint32_t)wa::dpp32<0x130, 0xf>(0, (int)b[t]);  // wave_shl:1: lane + 1's bits
       const uint32_t nx = lane == 63 ? (uint32_t)__builtin_amdgcn_readlane((int)b[t + 1], 0) : up;
-      const uint32_t v = ((b[t] | (nx << 16)) >> r.off) & 0xFFFFu;
+      const uint32_t x = ((b[t] | (nx << 16)) >> cur.off) & 0xFFFFu;
       // lanes 4k .. 4k+3 hold the 64 columns of word 16 t + k
-      const uint32_t lo = v | ((uint32_t)wa::dpp32<0x101, 0xf>(0, (int)v) << 16);  // row_shl:1
+      const uint32_t lo = x | ((uint32_t)wa::dpp32<0x101, 0xf>(0, (int)x) << 16);  // row_shl:1
       const uint32_t hi = (uint32_t)wa::dpp32<0x102, 0xf>(0, (int)lo);             // row_shl:2
       const int w = 16 * t + (lane >> 2);
-      if ((lane & 3) == 0 && w < nw) rowbits[(h * nw + w) * m + i] = (uint64_t)lo | ((uint64_t)hi << 32);
+      if ((lane & 3) == 0 && w < nw) words[r][w] = (uint64_t)lo | ((uint64_t)hi << 32);
     }
-  });
-}
-
-// Bit-packed columns from bit-packed rows, word-major: colbits[(h*mw + v)*n + j] bit r = M[h][64v + r][j].
-// One wavefront per (head, 64-column group, 64-row group): lane r holds row 64v + r's word.
-__global__ __launch_bounds__(256) void transpose_bits_kernel(const uint64_t* __restrict__ rowbits, int bh, int m,
-                                                             int n, int nw, int mw,
-                                                             uint64_t* __restrict__ colbits) {
-  const int64_t task = (int64_t)blockIdx.x * kWavesPerWG + (threadIdx.x >> 6);
-  const int64_t per_head = (int64_t)nw * mw;
-  if (task >= (int64_t)bh * per_head) return;
-  const int lane = threadIdx.x & 63;
-  const int64_t h = task / per_head;
-  const int rem = (int)(task % per_head);
-  const int cw = rem / mw;   // column word
-  const int v = rem % mw;    // row word
-  const int r = v * 64 + lane;
-  uint64_t out = r < m ? rowbits[(h * nw + cw) * m + r] : 0ull;
-  // 64 x 64 bit transpose (lane = row -> lane = column) by the recursive block swap: at distance s,
-  // a lane in the lower half of each 2s group trades its columns with bit s set for the partner's
-  // columns with bit s clear (six lane exchanges in place of 64 ballots)
+    cur = nr;
 #pragma unroll
-  for (int s = 32; s >= 1; s >>= 1) {
-    const uint64_t lo = s == 32 ? 0x00000000FFFFFFFFull : s == 16 ? 0x0000FFFF0000FFFFull
-                      : s == 8 ? 0x00FF00FF00FF00FFull : s == 4 ? 0x0F0F0F0F0F0F0F0Full
-                      : s == 2 ? 0x3333333333333333ull : 0x5555555555555555ull;  // columns with bit s clear
-    const uint32_t tlo = (uint32_t)__shfl_xor((int)(uint32_t)out, s);
-    const uint32_t thi = (uint32_t)__shfl_xor((int)(uint32_t)(out >> 32), s);
-    const uint64_t t = ((uint64_t)thi << 32) | tlo;
-    out = (lane & s) ? ((out & ~lo) | ((t >> s) & lo)) : ((out & lo) | ((t & lo) << s));
+    for (int t = 0; t < STEPS; ++t) c[t] = nc[t];
   }
-  const int j = cw * 64 + lane;
-  if (j < n) colbits[(h * mw + v) * n + j] = out;
+  __syncthreads();
+  int both = 0, any = 0;
+  for (int w = wv; w < nw; w += kPackWaves) {
+    uint64_t x = words[lane][w];  // row r0 + lane (zero past the head)
+    if (lane < rows) rowbits[(h * nw + w) * m + r0 + lane] = x;
+    const uint64_t y = (uint64_t)(uint32_t)wa::dpp32<0x130, 0xf>(0, (int)(uint32_t)x) |
+                       ((uint64_t)(uint32_t)wa::dpp32<0x130, 0xf>(0, (int)(uint32_t)(x >> 32)) << 32);
+    if (lane < 63 && lane + 1 < rows) {
+      both += __popcll(x & y);
+      any += __popcll(x | y);
+    }
+    // 64 x 64 bit transpose (lane = row -> lane = column) by the recursive block swap: at distance s,
+    // a lane in the lower half of each 2s group trades its columns with bit s set for the partner's
+    // columns with bit s clear
+#pragma unroll
+    for (int s = 32; s >= 1; s >>= 1) {
+      const uint64_t lo = s == 32 ? 0x00000000FFFFFFFFull : s == 16 ? 0x0000FFFF0000FFFFull
+                        : s == 8 ? 0x00FF00FF00FF00FFull : s == 4 ? 0x0F0F0F0F0F0F0F0Full
+                        : s == 2 ? 0x3333333333333333ull : 0x5555555555555555ull;  // columns with bit s clear
+      const uint32_t tlo = (uint32_t)__shfl_xor((int)(uint32_t)x, s);
+      const uint32_t thi = (uint32_t)__shfl_xor((int)(uint32_t)(x >> 32), s);
+      const uint64_t t = ((uint64_t)thi << 32) | tlo;
+      x = (lane & s) ? ((x & ~lo) | ((t >> s) & lo)) : ((x & lo) | ((t & lo) << s));
+    }
+    const int j = 64 * w + lane;
+    if (j < n) colbits[(h * mw + v) * n + j] = x;
+  }
+  both = wa::lane_prefix_sum(both);
+  any = wa::lane_prefix_sum(any);
+  if (lane == 63) part[wv] = make_int2(both, any);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int2 s = make_int2(0, 0);
+    for (int k = 0; k < kPackWaves; ++k) {
+      s.x += part[k].x;
+      s.y += part[k].y;
+    }
+    adj[h * mw + v] = s;
+  }
 }
 
 // Permutation check: one workgroup per head marks each entry in an LDS bitmap; an entry out of
@@ -323,21 +364,13 @@ hipError_t wa_launch_row_write(const uint8_t* mask, int bh, int mb, int n, const
   return hipGetLastError();
 }
 
-hipError_t wa_launch_pack_rows(const uint8_t* mask, int64_t rows, int m, int n, uint64_t* rowbits,
-                               int32_t* row_nnz, hipStream_t stream) {
-  if (rows <= 0) return hipSuccess;
-  const int nw = (n + 63) / 64;
-  WA_SCAN(pack_rows_kernel, rows, n, mask, (int)rows, m, n, nw, rowbits, row_nnz);
-  return hipGetLastError();
-}
-
-hipError_t wa_launch_transpose_bits(const uint64_t* rowbits, int bh, int m, int n, uint64_t* colbits,
-                                    hipStream_t stream) {
+hipError_t wa_launch_pack(const uint8_t* mask, int bh, int m, int n, uint64_t* rowbits, uint64_t* colbits,
+                          int32_t* row_nnz, int2* adj, hipStream_t stream) {
   const int nw = (n + 63) / 64, mw = (m + 63) / 64;
-  const int64_t tasks = (int64_t)bh * nw * mw;
-  if (tasks <= 0) return hipSuccess;
-  const int64_t grid = (tasks + kWavesPerWG - 1) / kWavesPerWG;
-  hipLaunchKernelGGL(transpose_bits_kernel, dim3((unsigned)grid), dim3(256), 0, stream, rowbits, bh, m, n, nw, mw,
-                     colbits);
+  if (bh <= 0 || m <= 0 || n <= 0) return hipSuccess;
+  const int steps = (n + 15 + 1023) / 1024;
+  const dim3 g((unsigned)((int64_t)bh * mw)), t(64 * kPackWaves);
+  auto* f = steps <= 1 ? pack_kernel<1> : steps <= 2 ? pack_kernel<2> : steps <= 3 ? pack_kernel<3> : pack_kernel<kMaxSteps>;
+  hipLaunchKernelGGL(f, g, t, 0, stream, mask, m, n, nw, mw, rowbits, colbits, row_nnz, adj);
   return hipGetLastError();
 }
