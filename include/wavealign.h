@@ -126,8 +126,8 @@ const char* wa_last_error(void);
 /* Built-in skip-profile constants. */
 wa_status wa_default_skip_profile(wa_skip_profile* out);
 
-/* Query blocks resident per XCD for the attention kernel of this head_dim and
- * block (32 CUs per XCD x workgroups per CU). Queries the current device. */
+/* Query blocks of a wave per XCD for this head_dim and block: 32 CUs per XCD x 2 (block
+ * 128), 4 (block 64, d 128) or 6 (block 64, d 64) workgroups. Queries the current device. */
 wa_status wa_wave_size(int32_t head_dim, int32_t block, int32_t* wave_per_xcd);
 
 /* Per-head mask statistics (Sec. II-B row NNZ n_i; Alg. 1 column counts c = M^T 1;

@@ -246,16 +246,14 @@ wa_status wa_wave_size(int32_t head_dim, int32_t block, int32_t* wave_per_xcd) {
   if (!wave_per_xcd) return fail(WA_ERR_INVALID_ARG, "wave_per_xcd is null");
   if ((head_dim != 64 && head_dim != 128) || (block != 64 && block != 128))
     return fail(WA_ERR_UNSUPPORTED, "head_dim %d / block %d not supported", head_dim, block);
-  int dev = 0, cus = 0, wgs = 0;
+  int dev = 0, cus = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
   e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return hip_fail(e, "hipDeviceGetAttribute");
-  e = wa_attention_occupancy(head_dim, block, &wgs);
-  if (e != hipSuccess) return hip_fail(e, "occupancy query");
   // 8 XCDs share the compute units evenly on MI355X (256 CUs = 8 x 32)
   const int per_xcd = cus >= 8 ? cus / 8 : cus;
-  *wave_per_xcd = per_xcd * (wgs > 0 ? wgs : 1);
+  *wave_per_xcd = per_xcd * wa::wave_wgs(head_dim, block);
   return ok();
 }
 

@@ -321,8 +321,9 @@ __device__ void fetch_task(Args a, bool first, Task* t) {
   t->bh = -1;
 }
 
+// Wavefronts a SIMD: 256 registers a lane leave room for two; the smallest tiles fit in 168 (three).
 template <int D, int BLK>
-__global__ __launch_bounds__(BLK * 2, 2) void attn_fwd_kernel(WaAttnLaunch) {
+__global__ __launch_bounds__(BLK * 2, D == 64 && BLK == 64 ? 3 : 2) void attn_fwd_kernel(WaAttnLaunch) {
   using C = Cfg<D, BLK>;
   __shared__ __attribute__((aligned(1024))) unsigned char k_lds[C::TBYTES];
   __shared__ __attribute__((aligned(1024))) unsigned char v_lds[C::TBYTES];
@@ -595,14 +596,14 @@ __global__ __launch_bounds__(BLK * 2, 2) void attn_fwd_kernel(WaAttnLaunch) {
 
     // ---- epilogue: merge the chunks of a split row, normalise and store at the original rows ----
     const float ltot = l_run + __shfl_xor(l_run, 32);
+    // the thread's offsets from an opaque copy of its index, so that none is held across the block loop
+    int tid_o = threadIdx.x;
+    asm volatile("" : "+v"(tid_o));
+    const int hf_o = (tid_o >> 5) & 1;
+    const int qloc = (tid_o >> 6) * 32 + (tid_o & 31);
+    const int qi_o = row * BLK + qloc;
     if (chunks > 1) {
-      // the thread's offsets from an opaque copy of its index, so that none is held across the block loop
-      int tid_o = tid;
-      asm volatile("" : "+v"(tid_o));
       const Args a = kernel_args();
-      const int hf_o = (tid_o >> 5) & 1;
-      const int qloc = (tid_o >> 6) * 32 + (tid_o & 31);
-      const int qi_o = row * BLK + qloc;
       // Partial tile of this chunk: O in 16-byte pieces [register quad][thread], then the row maxima and
       // the row sums. Device-scope stores (they go through to the level every XCD sees), completed before
       // the arrival is counted; the last arrival acquires and merges every tile in chunk order.
@@ -617,10 +618,10 @@ __global__ __launch_bounds__(BLK * 2, 2) void attn_fwd_kernel(WaAttnLaunch) {
         __hip_atomic_store(mine + BLK * D + qloc, m_run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(mine + BLK * D + BLK + qloc, ltot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
-      if (bad_kv && tid == 0 && a->status) atomicOr(a->status, 2);
+      if (bad_kv && tid_o == 0 && a->status) atomicOr(a->status, 2);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __syncthreads();
-      if (tid == 0) redo = atomicAdd(a->split + wa::split_arrival(a->split_cap, tile), 1);
+      if (tid_o == 0) redo = atomicAdd(a->split + wa::split_arrival(a->split_cap, tile), 1);
       __syncthreads();
       const int arrived = __builtin_amdgcn_readfirstlane(redo);
       __syncthreads();  // every wavefront has read the count before the next task clears it
@@ -688,13 +689,13 @@ __global__ __launch_bounds__(BLK * 2, 2) void attn_fwd_kernel(WaAttnLaunch) {
     }
     const float inv = ltot > 0.f ? 1.f / ltot : 0.f;
     const Args ae = kernel_args();
-    if (qi < n) {
-      uint16_t* og = (uint16_t*)ae->o + ((int64_t)bh * n + qi) * D;
+    if (qi_o < n) {
+      uint16_t* og = (uint16_t*)ae->o + ((int64_t)bh * n + qi_o) * D;
 #pragma unroll
       for (int dt = 0; dt < C::DT; ++dt)
 #pragma unroll
         for (int h2 = 0; h2 < 2; ++h2) {
-          const int col = dt * 32 + 16 * h2 + 8 * hf;
+          const int col = dt * 32 + 16 * h2 + 8 * hf_o;
           uint4 st;
           st.x = pack_bf16x2(oacc[dt][8 * h2 + 0] * inv, oacc[dt][8 * h2 + 1] * inv);
           st.y = pack_bf16x2(oacc[dt][8 * h2 + 2] * inv, oacc[dt][8 * h2 + 3] * inv);
@@ -702,10 +703,10 @@ __global__ __launch_bounds__(BLK * 2, 2) void attn_fwd_kernel(WaAttnLaunch) {
           st.w = pack_bf16x2(oacc[dt][8 * h2 + 6] * inv, oacc[dt][8 * h2 + 7] * inv);
           *(uint4*)(og + col) = st;
         }
-      if (ae->lse && hf == 0)
-        ae->lse[(int64_t)bh * n + qi] = ltot > 0.f ? (m_run + __log2f(ltot)) * kLn2 : -INFINITY;
+      if (ae->lse && hf_o == 0)
+        ae->lse[(int64_t)bh * n + qi_o] = ltot > 0.f ? (m_run + __log2f(ltot)) * kLn2 : -INFINITY;
     }
-    if (bad_kv && tid == 0 && ae->status) atomicOr(ae->status, 2);
+    if (bad_kv && tid_o == 0 && ae->status) atomicOr(ae->status, 2);
   }
 }
 
@@ -742,10 +743,11 @@ hipError_t launch_t(const WaAttnLaunch& a, hipStream_t stream) {
   hipError_t e = occ_t<D, BLK>(&occ);
   if (e != hipSuccess) return e;
   const int64_t slots = (int64_t)resident_cus() * std::max(occ, 1);
-  const int64_t grid = std::min<int64_t>(tasks, slots);
+  // the tail order's rule counts the workgroups of a wave
+  const int64_t grid = std::min<int64_t>(tasks, (int64_t)resident_cus() * wa::wave_wgs(D, BLK));
   if ((e = wa_launch_attn_prep(a, (int)grid, (int)slots, stream)) != hipSuccess || tasks <= 0) return e;
   // split rows give work to every resident workgroup, however few the rows
-  hipLaunchKernelGGL((attn_fwd_kernel<D, BLK>), dim3((unsigned)(a.split_cap > 0 ? slots : grid)), dim3(BLK * 2), 0,
+  hipLaunchKernelGGL((attn_fwd_kernel<D, BLK>), dim3((unsigned)(a.split_cap > 0 ? slots : std::min(tasks, slots))), dim3(BLK * 2), 0,
                      stream, a);
   return hipGetLastError();
 }
@@ -798,13 +800,5 @@ hipError_t wa_launch_attention(const WaAttnLaunch& a, hipStream_t stream) {
   if (a.head_dim == 64 && a.block == 128) return launch_t<64, 128>(a, stream);
   if (a.head_dim == 128 && a.block == 64) return launch_t<128, 64>(a, stream);
   if (a.head_dim == 64 && a.block == 64) return launch_t<64, 64>(a, stream);
-  return hipErrorInvalidValue;
-}
-
-hipError_t wa_attention_occupancy(int head_dim, int block, int* wgs_per_cu) {
-  if (head_dim == 128 && block == 128) return occ_t<128, 128>(wgs_per_cu);
-  if (head_dim == 64 && block == 128) return occ_t<64, 128>(wgs_per_cu);
-  if (head_dim == 128 && block == 64) return occ_t<128, 64>(wgs_per_cu);
-  if (head_dim == 64 && block == 64) return occ_t<64, 64>(wgs_per_cu);
   return hipErrorInvalidValue;
 }

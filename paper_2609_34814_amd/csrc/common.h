@@ -24,6 +24,10 @@ __host__ __device__ inline void xcd_segment(int x, int m, int n_xcd, const int32
   }
 }
 
+// Workgroups per compute unit of a wave (Sec. IV-D): part of the definition of the default permutation and of
+// the tail order, so fixed per shape rather than following the kernel's occupancy as it changes.
+__host__ __device__ constexpr int wave_wgs(int d, int block) { return block == 128 ? 2 : d == 128 ? 4 : 6; }
+
 // Scheduler state of one attention call, in the caller's workspace: a task counter per queue
 // (queue x holds segment x of every head, heads in order) and, per queue, the prefix sums of its
 // segment lengths over the heads.
@@ -148,7 +152,6 @@ hipError_t wa_launch_attn_prep(const WaAttnLaunch& a, int grid, int slots, hipSt
 hipError_t wa_noalloc_scratch(int32_t** ptr, size_t* bytes, int32_t** split, size_t* split_bytes);
 hipError_t wa_launch_transpose_v(const void* v, void* vt, int64_t bh, int seq_len, int mb, int head_dim, int block,
                                  hipStream_t stream);
-hipError_t wa_attention_occupancy(int head_dim, int block, int* wgs_per_cu);
 size_t wa_vt_bytes(int64_t bh, int mb, int head_dim, int block);
 
 hipError_t wa_launch_row_count(const uint8_t* mask, int64_t rows, int n, int32_t* counts, int64_t count_stride_rows,

@@ -52,3 +52,11 @@ def test_rows_of_one_angle_and_many_heads(blocks):
         assert np.array_equal(got[:, :3].cpu().numpy(), perm)
         srt = got.sort(dim=-1).values
         assert bool((srt == torch.arange(wl.mb, device="cuda", dtype=torch.int32)).all())
+
+
+def test_wave_sizes_do_not_follow_the_kernel():
+    """The default wave is part of what a default permutation is: fixed per shape (32 compute units per XCD)."""
+    import paper_2609_34814_amd as W
+    cus = torch.cuda.get_device_properties(0).multi_processor_count // 8
+    want = {(64, 64): 6, (64, 128): 2, (128, 64): 4, (128, 128): 2}
+    assert {k: W.wave_size(*k) for k in want} == {k: cus * v for k, v in want.items()}
