@@ -174,12 +174,8 @@ wa_status check_attn_common(const void* q, const void* k, const void* v, void* o
 }
 
 wa_status launch_compact(const uint8_t* mask, const Dims& d, int32_t* row_ptr, int32_t* col_idx, hipStream_t st) {
-  hipError_t e = wa_launch_row_count(mask, d.bh * d.mb, d.mb, row_ptr, d.mb + 1, 1, d.mb, st);
-  if (e != hipSuccess) return hip_fail(e, "row_count launch");
-  e = wa_launch_head_scan(row_ptr, (int)d.bh, d.mb, st);
-  if (e != hipSuccess) return hip_fail(e, "head_scan launch");
-  e = wa_launch_row_write(mask, (int)d.bh, d.mb, d.mb, row_ptr, nullptr, col_idx, st);
-  if (e != hipSuccess) return hip_fail(e, "row_write launch");
+  const hipError_t e = wa_launch_compact(mask, (int)d.bh, d.mb, row_ptr, col_idx, st);
+  if (e != hipSuccess) return hip_fail(e, "compaction launch");
   return WA_OK;
 }
 

@@ -154,6 +154,9 @@ hipError_t wa_launch_transpose_v(const void* v, void* vt, int64_t bh, int seq_le
                                  hipStream_t stream);
 size_t wa_vt_bytes(int64_t bh, int mb, int head_dim, int block);
 
+// row_ptr and the packed lists of every head
+hipError_t wa_launch_compact(const uint8_t* mask, int bh, int mb, int32_t* row_ptr, int32_t* col_idx,
+                             hipStream_t stream);
 hipError_t wa_launch_row_count(const uint8_t* mask, int64_t rows, int n, int32_t* counts, int64_t count_stride_rows,
                                int counts_offset, int mb, hipStream_t stream);
 hipError_t wa_launch_head_scan(int32_t* row_ptr, int bh, int mb, hipStream_t stream);

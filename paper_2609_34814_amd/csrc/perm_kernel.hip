@@ -794,7 +794,7 @@ __device__ __forceinline__ int64_t combine_digits(const v4i& acc) {
 
 // ---------------------------------------------------------------------------------------------
 // Heads of at most kMfmaMax blocks: the whole permutation in one workgroup of NT threads, one row and column
-// a thread (NT = 256, 512 or 1024). A wavefront takes four 16-line tiles of both products and holds their
+// a thread (NT = 256, 512 or 1024). A wavefront takes up to four 16-line tiles of both products and holds their
 // mask words in registers through every step, so a step touches no memory outside the compute unit; what
 // bounds it is the chain of its five barriers, reductions and the fp64 factor, which every wavefront
 // computes: with 16 wavefronts on a head of 256 blocks each reduction took 2,000 cycles or more, since
@@ -821,9 +821,10 @@ __device__ __forceinline__ void put_digits(int8_t* dg, int row0, int32_t v) {
   *(uint32_t*)(dg + (row0 + digit) * STRIDE + 32 * (tid >> 5) + 4 * (lane & 7)) = o;
 }
 
-template <typename C>
+// T: tiles a wavefront takes at most.
+template <typename C, int T>
 struct WaveWords {
-  static constexpr int T = 4, G = C::CAP / 256;  // tiles a wavefront, groups of four words a line
+  static constexpr int G = C::CAP / 256;  // groups of four words a line
   uint64_t w[G][T];  // [word group g][tile k]: word 4 g + q of line 16 (wave + NW k) + r
   __device__ __forceinline__ void load(const uint64_t* bits, int lines, int words) {
     const int lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4;
@@ -872,7 +873,7 @@ struct WaveWords {
   }
 };
 
-template <int NT>
+template <int NT, int T>
 __global__ __launch_bounds__(NT) void perm_mfma_kernel(WaPermLaunch a) {
   using C = Cfg<NT, NT>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
@@ -888,7 +889,7 @@ __global__ __launch_bounds__(NT) void perm_mfma_kernel(WaPermLaunch a) {
   const int m = a.m, n = a.n;
   const int64_t mm = m;
   const Head H = head_of(a, h);
-  WaveWords<C> cols, rows;
+  WaveWords<C, T> cols, rows;
   cols.load(H.colbits, n, H.mw);
   rows.load(H.rowbits, m, H.nw);
   sh.cc[tid] = cc;
@@ -1302,15 +1303,15 @@ __global__ void fp64_probe_kernel(const double* a, const double* b, const int64_
 
 }  // namespace
 
-template <int NT>
+template <int NT, int T>
 static hipError_t launch_fused(const WaPermLaunch& a, hipStream_t stream) {
   using C = Cfg<NT, NT>;
   constexpr size_t smem = ((sizeof(Shared<C>) + 15) & ~(size_t)15) + sizeof(MfmaLds<C>);
   static_assert(smem <= 160 * 1024, "the one-workgroup form fits one workgroup's LDS");
   const hipError_t e =
-      hipFuncSetAttribute((const void*)perm_mfma_kernel<NT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+      hipFuncSetAttribute((const void*)perm_mfma_kernel<NT, T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((perm_mfma_kernel<NT>), dim3(a.bh), dim3(NT), smem, stream, a);
+  hipLaunchKernelGGL((perm_mfma_kernel<NT, T>), dim3(a.bh), dim3(NT), smem, stream, a);
   return hipGetLastError();
 }
 
@@ -1323,9 +1324,12 @@ hipError_t wa_launch_perm(const WaPermLaunch& launch, hipStream_t stream) {
   if (a.m > MAXB || a.n > MAXB) return hipErrorInvalidValue;
   const int lines = a.m > a.n ? a.m : a.n;
   if (!a.stats_only && lines <= kMfmaMax) {
-    if (lines <= 256) return launch_fused<256>(a, stream);
-    if (lines <= 512) return launch_fused<512>(a, stream);
-    return launch_fused<1024>(a, stream);
+    // (512 threads for heads of 256 blocks: 61 us a call of 12 heads against 52)
+    if (lines <= 64) return launch_fused<256, 1>(a, stream);
+    if (lines <= 128) return launch_fused<256, 2>(a, stream);
+    if (lines <= 256) return launch_fused<256, 4>(a, stream);
+    if (lines <= 512) return launch_fused<512, 4>(a, stream);
+    return launch_fused<1024, 4>(a, stream);
   }
   hipError_t e;
   if (a.stats_only || a.skip_mode == SKIP_ALWAYS) {
