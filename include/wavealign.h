@@ -218,12 +218,12 @@ wa_status wa_produce_block_mask(const void* q, const void* k, const wa_shape* sh
  * must not overlap. */
 wa_status wa_mask_producer_workspace_size(const wa_shape* shape, size_t* bytes);
 
-/* Workspace bytes needed by wa_sparse_attn: the scheduler state (queue counters,
+/* Workspace bytes needed by wa_sparse_attn: the scheduler state (the
  * per-queue prefix tables and the per-queue order of the last heads: 64 + 64 * (B*H + 1)
  * int32 rounded up to 64 entries, plus 64 * T * M_B int32 with T = min(B*H, 16384 / M_B, 256)
  * rounded up to 64 entries, plus 64 + B*H*M_B int32 for the head-interleaved order,
- * rounded up to 256 bytes), the state of split rows (launches of up to 2^22 / block query
- * blocks: at most 32 MiB of float32 tiles, their tasks and counters),
+ * rounded up to 256 bytes), the task counters (8.25 KiB) with the state of split rows (launches of up to
+ * 2^22 / block query blocks: at most 32 MiB of float32 tiles, their tasks and counters),
  * a zero-padded transposed copy of V (bf16 [B][H][head_dim][M_B*block], rounded up
  * to 256 bytes), then the compacted lists. The parts before the lists
  * suffice for wa_sparse_attn_csr. Calls that share a workspace must not overlap. */
@@ -325,10 +325,10 @@ wa_status wa_sparse_attn_vt(const void* q, const void* k, const void* vt, const 
 
 /* For callers that cannot allocate device memory: code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc. The same computation as
- * wa_sparse_attn_vt, with the scheduler state (queue counters, prefix tables, the
+ * wa_sparse_attn_vt, with the scheduler state (prefix tables, the
  * orders of the last heads and the head-interleaved table) kept in a static device
  * array of the library instead of a workspace: WA_NOALLOC_SCRATCH_BYTES per GPU (and
- * 32.25 MiB for the state of split rows), taken when the library's code is loaded on
+ * 32.25 MiB for the task counters and the state of split rows), taken when the library's code is loaded on
  * that GPU and held until the process ends. The call allocates and frees nothing. A shape whose state needs more
  * (64 + n_xcd*(B*H+1) rounded up to 64, + n_xcd*T*M_B rounded up to 64, + 64 + B*H*M_B
  * int32, T as for wa_attn_workspace_size) is rejected with WA_ERR_WORKSPACE before

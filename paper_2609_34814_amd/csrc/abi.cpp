@@ -122,13 +122,13 @@ void perm_ws_pointers(WaPermLaunch& a, const PermWs& L, char* base) {
   a.stats = (PermStats*)(base + L.stats);
 }
 
-// Attention workspace: [scheduler state][split rows][V^T copy][row_ptr][col_idx]; the CSR entry point
+// Attention workspace: [scheduler state][task counters and split rows][V^T copy][row_ptr][col_idx]; the CSR entry point
 // uses the first three parts, the V^T one the first two. The scheduler part is sized for the largest n_xcd.
 constexpr int kMaxXcd = 64;
 size_t attn_order_bytes(const Dims& d) { return align_up(wa::sched_state_ints(d.bh, d.mb, kMaxXcd) * 4); }
 size_t attn_split_bytes(const Dims& d) {
   const int cap = wa::split_cap(d.bh, d.mb, d.blk, d.d);
-  return cap > 0 ? align_up(wa::split_ints(cap) * 4 + cap * wa::part_tile_floats(d.blk, d.d) * 4) : 0;
+  return align_up(wa::split_ints(cap) * 4 + cap * wa::part_tile_floats(d.blk, d.d) * 4);
 }
 size_t attn_sched_bytes(const Dims& d) { return attn_order_bytes(d) + attn_split_bytes(d); }
 size_t attn_csr_ws_bytes(const Dims& d) {
@@ -181,7 +181,7 @@ wa_status launch_compact(const uint8_t* mask, const Dims& d, int32_t* row_ptr, i
 
 // v: V in its natural layout (transposed into the workspace after the scheduler state), or null with
 // vt: V already transposed by the caller. The lists come packed (row_ptr) or at a fixed stride (row_cnt).
-// split: the split rows' memory, attn_split_bytes(d).
+// split: the task counters and the split rows' memory, attn_split_bytes(d).
 wa_status launch_attn(const void* q, const void* k, const void* v, const void* vt, void* ws, void* split,
                       const int32_t* row_ptr, const int32_t* row_cnt, const int32_t* col_idx, const int32_t* perm,
                       const int32_t* seg, const Dims& d, float scale, int32_t n_xcd, int32_t head_order, void* o,

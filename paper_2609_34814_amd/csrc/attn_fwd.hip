@@ -230,7 +230,9 @@ struct Task {
 // The first task of workgroup b is fixed: the chunks of the split rows go to workgroups 0, 1, ..., and the
 // first entries of queue x to the workgroups after them with b mod n_xcd = x, in order. Only later
 // tasks are taken with atomic counters: an atomic on one address costs about 0.1 us of device time,
-// whoever issues it, so a launch whose 512 to 1,536 workgroups all began with one spent 50 us and more.
+// whoever issues it, so a launch whose 512 to 1,536 workgroups all began with one spent 50 us and more. The
+// chunks past the first of each workgroup have a counter per shard (workgroups b mod kSplitShards), read
+// before it is added to: with one counter for all, 8 x 120 rows of 11 blocks of 64 in 1,850 chunks took 182 us, now 82.
 __device__ __forceinline__ int first_wg(int x, int split, int n_xcd) {  // of queue x's first entry
   return split + (x + n_xcd - split % n_xcd) % n_xcd;
 }
@@ -281,42 +283,68 @@ __device__ bool queue_task(Args a, int x, int t, int longest, Task* out) {
 }
 
 __device__ void split_task(Args a, int k, Task* out) {
-  const int4 e = ((const int4*)(a->split + 64))[k];
+  const int4 e = ((const int4*)(a->split + wa::kSplitHead))[k];
   int beg, end;
   wa::row_range(a, e.x, e.y, &beg, &end);
   const int n = end - beg, c = e.z & 0xFFFF, chunks = e.z >> 16;
   *out = {e.x, e.y, beg + n * c / chunks, beg + n * (c + 1) / chunks, chunks, c, e.w};
 }
 
-// Next task of this workgroup, run by one lane: the chunks of the split rows first (the longest work),
-// then the queue of the workgroup's XCD, then the others. bh = -1 when nothing is left.
+// Next task of this workgroup, run by one wavefront (t: its first lane's): the chunks of the split rows first
+// (the longest work), then the queue of the workgroup's XCD, then the others. bh = -1 when nothing is left.
+// Lane x reads queue x's counter; with eight reads one after another the calls of 4 x 254 and 78 x 29 rows (d 128)
+// took 125 and 158 us, so 120 and 152.
 __device__ void fetch_task(Args a, bool first, Task* t) {
+  int lane = threadIdx.x & 63;
+  asm volatile("" : "+v"(lane));  // opaque: nothing per lane is held across the block loop
   const int b = blockIdx.x, wgs = gridDim.x;
   const int split = a->split_cap > 0 ? a->split[0] : 0;
-  const int longest = split > 0 ? a->split[2] : INT32_MAX;  // rows of more blocks are split
+  const int longest = split > 0 ? a->split[1] : INT32_MAX;  // rows of more blocks are split
   const int32_t* pre = a->sched + 64;
+  bool got = false;  // lane 0's
   if (first) {
-    if (b < split) return split_task(a, b, t);
+    if (b < split) {
+      if (lane == 0) split_task(a, b, t);
+      return;
+    }
     const int x = b % a->n_xcd, k = (b - first_wg(x, split, a->n_xcd)) / a->n_xcd;
-    if (k < pre[(int64_t)x * (a->bh + 1) + a->bh] && queue_task(a, x, k, longest, t)) return;
+    if (k < pre[(int64_t)x * (a->bh + 1) + a->bh]) {
+      if (lane == 0) got = queue_task(a, x, k, longest, t);
+      if (__ballot(got)) return;
+    }
   }
   if (split > wgs) {
-    const int k = wgs + atomicAdd(a->split + 1, 1);
-    if (k < split) return split_task(a, k, t);
+    const int shards = min(wa::kSplitShards, wgs), s = b % shards;
+    const int count = (split - wgs - s + shards - 1) / shards;  // chunks wgs + s, wgs + s + shards, ...
+    int32_t* cnt = a->split + wa::split_counter(s);
+    if (lane == 0 && __hip_atomic_load(cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < count) {
+      const int k = atomicAdd(cnt, 1);
+      got = k < count;
+      if (got) split_task(a, wgs + s + k * shards, t);
+    }
+    if (__ballot(got)) return;
   }
   const int home = (int)(__builtin_amdgcn_s_getreg((3 << 11) | (0 << 6) | 20) & 0xF) % a->n_xcd;
-  for (int i = 0; i < a->n_xcd; ++i) {
-    const int x = (home + i) % a->n_xcd;
-    const int total = pre[(int64_t)x * (a->bh + 1) + a->bh];
-    const int w0 = first_wg(x, split, a->n_xcd);
-    const int given = w0 < wgs ? (wgs - w0 + a->n_xcd - 1) / a->n_xcd : 0;  // entries with a fixed workgroup
-    if (given >= total) continue;
-    int32_t* cnt = a->sched + x;
-    while (given + __hip_atomic_load(cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < total) {
-      const int k = given + atomicAdd(cnt, 1);
-      if (k >= total) break;
-      if (queue_task(a, x, k, longest, t)) return;
+  int given = 0, total = 0;
+  if (lane < a->n_xcd) {
+    total = pre[(int64_t)lane * (a->bh + 1) + a->bh];
+    const int w0 = first_wg(lane, split, a->n_xcd);
+    given = w0 < wgs ? (wgs - w0 + a->n_xcd - 1) / a->n_xcd : 0;  // entries with a fixed workgroup
+  }
+  for (;;) {
+    // queues with entries left; a counter only grows, so the loop ends when every queue is drained
+    bool left = given < total;
+    if (left) left = given + __hip_atomic_load(a->split + wa::queue_counter(lane, a->n_xcd), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < total;
+    const uint64_t mask = __ballot(left);
+    if (mask == 0) break;
+    const uint64_t from_home = mask >> home << home;
+    const int x = __ffsll((unsigned long long)(from_home ? from_home : mask)) - 1;
+    const int x_given = __shfl(given, x), x_total = __shfl(total, x);
+    if (lane == 0) {
+      const int k = x_given + atomicAdd(a->split + wa::queue_counter(x, a->n_xcd), 1);
+      got = k < x_total && queue_task(a, x, k, longest, t);
     }
+    if (__ballot(got)) return;
   }
   t->bh = -1;
 }
@@ -352,11 +380,13 @@ __global__ __launch_bounds__(BLK * 2, D == 64 && BLK == 64 ? 3 : 2) void attn_fw
   }
 
   for (bool first = true;; first = false) {
-    if (tid == 0) {
+    if (w == 0) {
       Task t;
       fetch_task(kernel_args(), first, &t);
-      task = t;
-      redo = 0;
+      if (tid == 0) {
+        task = t;
+        redo = 0;
+      }
     }
     __syncthreads();
     const int bh = __builtin_amdgcn_readfirstlane(task.bh);

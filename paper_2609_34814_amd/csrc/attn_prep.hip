@@ -8,9 +8,11 @@ namespace {
 
 // L of the split plan: this share of the kept blocks per resident workgroup. Without the split, a launch
 // of few rows lasts as long as its longest row: 2 x 64 rows of 64-token blocks (d 64, 24% kept) took
-// 61 us in this kernel, 8 x 61 ragged rows (d 128, 25%) 148 us; with it 20 and 92 us. 12 x 512 rows of
-// 64-token blocks: 920 -> 850 us.
-constexpr int kSplitNum = 3, kSplitDen = 4;
+// 61 us in this kernel, 8 x 61 ragged rows (d 128, 25%) 148 us; with it 20 and 86 us. A smaller share
+// makes more chunks than the launch has workgroups, a larger one longer ends: at 3/4, 1, 5/4 and 3/2 calls
+// of 20 x 317 rows of 64 blocks (21% kept) took 720, 648, 632 and 631 us, 12 x 512 rows (d 128) of 64-token
+// blocks 836, 850, 845 and 881, 8 x 208 rows (d 64) 195, 187, 186 and 182 us.
+constexpr int kSplitNum = 5, kSplitDen = 4;
 
 // ---------------------------------------------------------------------------------------------
 // Preparation: everything a call needs before the attention kernel, in one launch, so that the latency
@@ -34,11 +36,15 @@ __device__ __forceinline__ int wg_scan(int v, int32_t* part, int* all) {
   return v + before;
 }
 
+// Late entries up to this many are placed by counting (four wavefronts: 1.3 us at 256, where the bitonic stages
+// take 4), more by a bitonic sort.
+constexpr int kRankLate = 256;
+
 struct OrderLds {
   int32_t hstart[wa::kTailMaxHeads + 1];  // first entry of each head's segment
   int32_t hslot0[wa::kTailMaxHeads];      // its first slot
   int32_t part[PW];
-  uint32_t key[wa::kTailEntries];
+  __attribute__((aligned(16))) uint32_t key[wa::kTailEntries];
 };
 struct TransposeLds {
   uint16_t t[PT / 256][64][64 + 8];
@@ -57,7 +63,7 @@ __device__ void queue_prefix(const WaAttnLaunch& a, OrderLds& L, int x) {
   const int t = threadIdx.x;
   int32_t* px = a.sched + 64 + (int64_t)x * (a.bh + 1);
   if (t == 0) {
-    a.sched[x] = 0;
+    a.split[wa::queue_counter(x, a.n_xcd)] = 0;
     px[0] = 0;
   }
   int carry = 0;
@@ -159,7 +165,7 @@ __device__ void tail_order(const WaAttnLaunch& a, OrderLds& L, int x, int grid) 
   int lg = 0;
   while ((1 << lg) < nlate) ++lg;
   const int P = 1 << lg;
-  for (int i = nlate + t; i < P; i += PT) L.key[i] = 0xFFFFFFFFu;
+  for (int i = nlate + t; i < max(P, (nlate + 3) & ~3); i += PT) L.key[i] = 0xFFFFFFFFu;
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
     const int e = e0 + i;
@@ -171,10 +177,28 @@ __device__ void tail_order(const WaAttnLaunch& a, OrderLds& L, int x, int grid) 
       }
     }
   }
-  // Late entries: bitonic sort ascending = descending block count, ties in queue order. A pair at a
-  // distance of at most 64 lies within the 128 entries of one wavefront's threads, so those stages
-  // need no workgroup barrier (a wavefront's LDS operations complete in order).
+  // Late entries ascending by key = descending block count, ties in queue order.
+  auto place = [&](int pos, uint32_t key) {
+    const int e = (int)(key & 0x3FFFu);
+    const int k = head_of(e);
+    tail[pos] = (k << 16) | (L.hslot0[k] + (e - L.hstart[k]));
+  };
   __syncthreads();
+  if (nlate <= kRankLate) {
+    // few: an entry's place is the number of smaller keys (padded to four a read with the largest key)
+    if (t < nlate) {
+      const uint32_t mine = L.key[t];
+      int r = 0;
+      for (int i = 0; i < nlate; i += 4) {
+        const uint4 x = *(const uint4*)&L.key[i];
+        r += (x.x < mine) + (x.y < mine) + (x.z < mine) + (x.w < mine);
+      }
+      place(r, mine);
+    }
+    return;
+  }
+  // Bitonic sort. A pair at a distance of at most 64 lies within the 128 entries of one wavefront's threads,
+  // so those stages need no workgroup barrier (a wavefront's LDS operations complete in order).
   for (int kk = 1; kk <= lg; ++kk)
     for (int lj = kk - 1; lj >= 0; --lj) {
       const int j = 1 << lj;
@@ -194,11 +218,7 @@ __device__ void tail_order(const WaAttnLaunch& a, OrderLds& L, int x, int grid) 
       }
     }
   __syncthreads();
-  for (int i = t; i < nlate; i += PT) {
-    const int e = (int)(L.key[i] & 0x3FFFu);
-    const int k = head_of(e);
-    tail[i] = (k << 16) | (L.hslot0[k] + (e - L.hstart[k]));
-  }
+  for (int i = t; i < nlate; i += PT) place(i, L.key[i]);
 }
 
 // Head-interleaved order of queue x: the queue's tasks round-robin over the
@@ -286,13 +306,13 @@ __device__ void split_plan(const WaAttnLaunch& a, OrderLds& S, int slots) {
     if (max(total, row_total) <= a.split_cap) break;
     L += (L + 1) / 2;
   }
+  if (t < wa::kSplitShards) a.split[wa::split_counter(t)] = 0;
   if (t == 0) {
     a.split[0] = total;
-    a.split[1] = 0;
-    a.split[2] = L;
+    a.split[1] = L;
   }
   if (total == 0) return;
-  int4* tasks = (int4*)(a.split + 64);
+  int4* tasks = (int4*)(a.split + wa::kSplitHead);
   int at = mine, h, r;
   for (int i = t; i < rows; i += PT) {
     const int n = slot_blocks(i, &h, &r);

@@ -28,9 +28,9 @@ __host__ __device__ inline void xcd_segment(int x, int m, int n_xcd, const int32
 // the tail order, so fixed per shape rather than following the kernel's occupancy as it changes.
 __host__ __device__ constexpr int wave_wgs(int d, int block) { return block == 128 ? 2 : d == 128 ? 4 : 6; }
 
-// Scheduler state of one attention call, in the caller's workspace: a task counter per queue
-// (queue x holds segment x of every head, heads in order) and, per queue, the prefix sums of its
-// segment lengths over the heads.
+// Scheduler state of one attention call, in the caller's workspace: per queue (queue x holds segment x of
+// every head, heads in order), from 64, the prefix sums of its segment lengths over the heads. The first 64
+// int32 are not used.
 __host__ __device__ inline size_t sched_ints(int64_t bh, int n_xcd) { return 64 + (size_t)n_xcd * (bh + 1); }
 
 // The last tail_heads(bh, m) heads of every queue run in an order built at each call (the tail
@@ -61,7 +61,10 @@ __host__ __device__ inline size_t sched_state_ints(int64_t bh, int m, int n_xcd)
 // split the same way in every execution order. The tiles take at most kPartBytes; L grows until
 // the chunks fit. Launches of more than kSplitMaxTokens / block rows never split: their rows are short
 // next to the launch (a row there outlasts its share of the launch only below 0.5% density).
-constexpr int kSplitMinBlocks = 8;  // shortest L
+// Shortest L. At 8 a launch of 44 x 29 rows of 4.6 of 64 blocks on average takes 47 us instead of 38 and one of 8 x 120
+// rows of 11 blocks 82 instead of 43 (the merge costs about as much as ten blocks); 2 x 64 rows take 29
+// instead of 31.
+constexpr int kSplitMinBlocks = 12;
 constexpr size_t kPartBytes = (size_t)32 << 20;
 constexpr int64_t kSplitMaxTokens = (int64_t)1 << 22;
 __host__ __device__ inline size_t part_tile_floats(int block, int d) { return (size_t)block * (d + 2); }
@@ -71,10 +74,18 @@ __host__ __device__ inline int split_cap(int64_t bh, int m, int block, int d) {
   const int64_t most = bh * m * ((m + kSplitMinBlocks - 1) / kSplitMinBlocks);
   return (int)(most < cap ? most : cap);
 }
-// Split state: [0] chunk tasks, [1] tasks taken, [2] L; from 64 the tasks {head, row, chunk | chunks << 16,
-// the row's first tile}; then one arrival counter per tile, 64 bytes apart (atomics on one line
-// serialise; the row's first tile counts the row).
-__host__ __device__ inline size_t split_arrival(int cap, int tile) { return 64 + 4 * (size_t)cap + 16 * (size_t)tile; }
+// Split state: [0] chunk tasks, [1] L; the counters of tasks taken, one per queue and one per shard of the
+// chunks; from kSplitHead the tasks {head, row, chunk | chunks << 16, the row's first tile}; then one arrival
+// counter per tile (the row's first tile counts the row), 64 bytes apart. The counters of tasks have
+// 4 KiB each for the queues and the shards, spread evenly: atomics on one line serialise across the device, and a
+// launch takes thousands. Eight queue counters in 32 bytes, 32 bytes apart and 512 bytes apart:
+// 70 x 83 rows (d 128) 454, 383 and 366 us, 20 x 338 rows of 64-token blocks (d 128) 648, 556 and 515 us.
+constexpr int kSplitShards = 8;
+constexpr int kCounterInts = 1024;
+constexpr int kSplitHead = 64 + 2 * kCounterInts;
+__host__ __device__ inline int queue_counter(int x, int n_xcd) { return 64 + x * (kCounterInts / n_xcd); }
+__host__ __device__ inline int split_counter(int shard) { return 64 + kCounterInts + shard * (kCounterInts / kSplitShards); }
+__host__ __device__ inline size_t split_arrival(int cap, int tile) { return kSplitHead + 4 * (size_t)cap + 16 * (size_t)tile; }
 __host__ __device__ inline size_t split_ints(int cap) { return (split_arrival(cap, cap) + 63) / 64 * 64; }
 
 // Lane moves through DPP (a few cycles, where a lane shuffle is an LDS round trip): lanes that the
@@ -104,9 +115,9 @@ struct WaAttnLaunch {
   const void* v;     // null when the caller passes V already transposed (vt)
   void* vt;          // V transposed to [bh][head_dim][mb*block], zero-padded: the caller's, or the
                      // workspace copy that the launch writes from v
-  int32_t* sched;    // workspace: sched_state_ints(bh, mb, n_xcd) int32 (counters at [0, n_xcd), prefix
-                     // tables at 64, the tail order table at tail_offset(bh, n_xcd))
-  int32_t* split;    // workspace: split_ints(split_cap) int32, then the tiles
+  int32_t* sched;    // workspace: sched_state_ints(bh, mb, n_xcd) int32 (prefix tables at 64, the tail order
+                     // table at tail_offset(bh, n_xcd))
+  int32_t* split;    // workspace: split_ints(split_cap) int32 (also with split_cap 0), then the tiles
   float* part;       // workspace: split_cap tiles of part_tile_floats(block, head_dim)
   int32_t split_cap;
   const int32_t* row_ptr;  // [bh][mb+1], row r's list at col_idx + head mb^2 + row_ptr[r]; null:

@@ -11,7 +11,7 @@ from oracle import attention as A   # noqa: E402
 from tests.gpu_util import bf16_dev, compare_blocks, dev_f64, u8_dev   # noqa: E402
 from workloads.gen import custom, make_qkv   # noqa: E402
 
-MIN_L = 8    # the shortest L: on launches this small, rows of more kept blocks are split
+MIN_L = 12   # the shortest L: on launches this small, rows of more kept blocks are split
 
 
 def _mask(heads, mb, rng):
@@ -99,3 +99,24 @@ def test_split_rows_up_to_the_tile_limit():
     ref = A.block_sparse_attention_rows(q, k, v, mask, block, picks)
     st = compare_blocks(dev_f64(o), ref, block, wl.seq_len, lse.cpu().numpy().astype(np.float64))
     assert st["max_abs"] <= 1e-2 and st["rel_rms"] <= 1e-2 and st["lse"] <= 1e-3, st
+
+
+@pytest.mark.parametrize("d,block,heads,mb,n", [(64, 64, 10, 100, 30), (128, 128, 8, 48, 20)])
+def test_more_chunks_than_workgroups(d, block, heads, mb, n):
+    """Rows of n blocks each, all in two chunks, and more chunks than the device holds workgroups: the chunks past
+    the first of each workgroup come from the shards' counters, every queue entry is a split row but one a head."""
+    import paper_2609_34814_amd as W
+    wl = custom("split-many", heads=heads, head_dim=d, block=block, grid=(1, 1, mb * block), seed=23)
+    rng = np.random.default_rng(n)
+    mask = np.zeros((1, heads, mb, mb), dtype=np.uint8)
+    for h in range(heads):
+        for i in range(mb):
+            mask[0, h, i, rng.permutation(mb)[: n if i else 1]] = 1
+    q, k, v = make_qkv(wl)
+    o, lse = W.sparse_attn(bf16_dev(q), bf16_dev(k), bf16_dev(v), u8_dev(mask), block=block, return_lse=True)
+    assert bool(torch.isfinite(o.float()).all()) and bool(torch.isfinite(lse).all())
+    picks = [(0, h, i) for h in range(heads) for i in (0, 1, h + 5, mb - 1)]
+    ref = A.block_sparse_attention_rows(q, k, v, mask, block, picks)
+    st = compare_blocks(dev_f64(o), ref, block, wl.seq_len, lse.cpu().numpy().astype(np.float64))
+    assert st["max_abs"] <= 4 * 2.0 ** -9 * float(np.abs(A.bf16_to_f64(v)).max()), st
+    assert st["rel_rms"] <= 1e-2 and st["lse"] <= 1e-3, st
