@@ -52,6 +52,8 @@
 
 #include <algorithm>
 #include <atomic>
+#include <cfloat>
+#include <cmath>
 #include <mutex>
 #include <type_traits>
 
@@ -621,7 +623,9 @@ __global__ __launch_bounds__(BLK * 2, D == 64 && BLK == 64 ? 3 : 2) void attn_fw
         mx = fmaxf(mx, tile_max(sacc));
         WA_BARRIER();  // every wavefront is done with the tile before the next copy
       }
-      m_run = mx;
+      // A chunk may hold only scores of -inf where its row does not: against the lowest float its
+      // probabilities are 0 (NaN scores stay NaN), and so is its weight next to any finite score.
+      m_run = fmaxf(mx, chunks > 1 ? -FLT_MAX : -INFINITY);
     }
 
     // ---- epilogue: merge the chunks of a split row, normalise and store at the original rows ----
@@ -704,7 +708,7 @@ __global__ __launch_bounds__(BLK * 2, D == 64 && BLK == 64 ? 3 : 2) void attn_fw
             }
           }
         }
-        inv = l > 0.f ? 1.f / l : 0.f;
+        inv = l > 0.f ? 1.f / l : NAN;  // a split row is not empty: its scores are -inf or NaN
         if (qi_o < n)
 #pragma unroll
           for (int j = 0; j < 2; ++j)

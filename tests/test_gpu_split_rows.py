@@ -120,3 +120,38 @@ def test_more_chunks_than_workgroups(d, block, heads, mb, n):
     st = compare_blocks(dev_f64(o), ref, block, wl.seq_len, lse.cpu().numpy().astype(np.float64))
     assert st["max_abs"] <= 4 * 2.0 ** -9 * float(np.abs(A.bf16_to_f64(v)).max()), st
     assert st["rel_rms"] <= 1e-2 and st["lse"] <= 1e-3, st
+
+
+@pytest.mark.parametrize("d,block", [(64, 64), (64, 128), (128, 64), (128, 128)])
+def test_split_rows_with_scores_of_minus_infinity(d, block):
+    """Chunks whose scores are all -inf (keys of the lower blocks hold -inf against positive queries) add nothing to
+    a row that has finite ones; a row of -inf alone has no value (NaN, lse -inf), split or not; NaN scores stay NaN."""
+    import paper_2609_34814_amd as W
+    mb = 3 * MIN_L + 5
+    n, low = mb * block - 7, 2 * MIN_L * block
+    g = torch.Generator().manual_seed(d + block)
+    q, k, v = (torch.randn(1, 1, n, d, generator=g).to(torch.bfloat16) for _ in range(3))
+    q[..., 0] = q[..., 0].abs() + 0.5
+    k[:, :, :low, 0] = -float("inf")
+    k[:, :, low + block, 1] = float("nan")
+    mask = torch.zeros(1, 1, mb, mb, dtype=torch.uint8)
+    mask[0, 0, :, :] = torch.eye(mb, dtype=torch.uint8)
+    mask[0, 0, 1, :] = 1
+    mask[0, 0, 1, low // block + 1] = 0        # split, -inf in its first chunks, finite in its last
+    mask[0, 0, 2, : low // block] = 1          # split, -inf alone
+    mask[0, 0, 3, :] = 1                       # split, with the NaN key
+    mask[0, 0, 4, [4, mb - 1]] = 1             # not split, -inf then finite
+    o, lse = W.sparse_attn(q.cuda(), k.cuda(), v.cuda(), mask.cuda(), block=block, return_lse=True)
+    o, lse = o.double().cpu()[0, 0], lse.double().cpu()[0, 0]
+    keep = mask[0, 0].bool().repeat_interleave(block, 0).repeat_interleave(block, 1)[:n, :n]
+    for row in (1, 4):
+        t = slice(row * block, (row + 1) * block)
+        keys = keep[row * block]
+        s = q[0, 0, t].double() @ k[0, 0, keys].double().T / d ** 0.5
+        want = torch.softmax(s, -1) @ v[0, 0, keys].double()
+        # bf16 probabilities and output: 2 * 2^-9 relative each, of values up to max|V|
+        assert float((o[t] - want).abs().max()) <= 4 * 2.0 ** -9 * float(v.double().abs().max()), row
+        assert float((lse[t] - torch.logsumexp(s, -1)).abs().max()) <= 1e-3, row
+    for row in (2, 3):
+        assert bool(torch.isnan(o[row * block:(row + 1) * block]).all()), row
+    assert bool(torch.isneginf(lse[2 * block:3 * block]).all())
