@@ -62,14 +62,16 @@ __device__ __forceinline__ uint32_t span_bits(const RowSpan& r, int k, const uin
   return bits & 0xFFFFu;
 }
 
-// Calls f(row, span, chunks) for the rows of this wavefront, the loads of the next row in flight.
-template <int STEPS, typename F>
+// Calls f(row, span, chunks) for the rows of this wavefront, the loads of the next row in flight. DOWN: from the last
+// row to the first.
+template <int STEPS, bool DOWN, typename F>
 __device__ __forceinline__ void for_rows(const uint8_t* mask, int rows, int n, F&& f) {
   const int lane = threadIdx.x & 63;
   const int stride = (int)gridDim.x * kWavesPerWG;
   int row = (int)blockIdx.x * kWavesPerWG + (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (row >= rows) return;
-  RowSpan cur = row_span(mask, row, n);
+  auto at = [&](int i) { return DOWN ? rows - 1 - i : i; };
+  RowSpan cur = row_span(mask, at(row), n);
   uint4 c[STEPS];
   load_span<STEPS>(cur, lane, c);
   for (;;) {
@@ -77,10 +79,10 @@ __device__ __forceinline__ void for_rows(const uint8_t* mask, int rows, int n, F
     RowSpan nr = cur;
     uint4 nc[STEPS];
     if (next < rows) {
-      nr = row_span(mask, next, n);
+      nr = row_span(mask, at(next), n);
       load_span<STEPS>(nr, lane, nc);
     }
-    f(row, cur, c);
+    f(at(row), cur, c);
     if (next >= rows) break;
     row = next;
     cur = nr;
@@ -89,13 +91,15 @@ __device__ __forceinline__ void for_rows(const uint8_t* mask, int rows, int n, F
   }
 }
 
-// counts[(row / mb) * stride + offset + row % mb] = n_row
+// counts[(row / mb) * stride + offset + row % mb] = n_row. From the last row to the first: the list writing that
+// follows starts at the rows read last, which the memory-side cache still holds (323 MB of mask, counts and
+// lists together: 150.7 us with both passes ascending, 144.1 so).
 template <int STEPS>
 __global__ __launch_bounds__(256) void row_count_kernel(const uint8_t* __restrict__ mask, int rows, int n,
                                                          int32_t* __restrict__ counts, int64_t stride, int offset,
                                                          int mb) {
   const int lane = threadIdx.x & 63;
-  for_rows<STEPS>(mask, rows, n, [&](int row, const RowSpan& r, const uint4 (&c)[STEPS]) {
+  for_rows<STEPS, true>(mask, rows, n, [&](int row, const RowSpan& r, const uint4 (&c)[STEPS]) {
     int cnt = 0;
 #pragma unroll
     for (int t = 0; t < STEPS; ++t) cnt += __popc(span_bits(r, 64 * t + lane, c[t]));
@@ -143,7 +147,7 @@ __global__ __launch_bounds__(256) void row_write_kernel(const uint8_t* __restric
   __shared__ uint16_t stage[kWavesPerWG][STEPS * 1024];
   const int lane = threadIdx.x & 63;
   uint16_t* st = stage[threadIdx.x >> 6];
-  for_rows<STEPS>(mask, rows, n, [&](int row, const RowSpan& r, const uint4 (&c)[STEPS]) {
+  for_rows<STEPS, false>(mask, rows, n, [&](int row, const RowSpan& r, const uint4 (&c)[STEPS]) {
     const int h = row / mb;
     int32_t* out = row_ptr ? col_idx + (int64_t)h * mb * n + row_ptr[(int64_t)h * (mb + 1) + (row - h * mb)]
                            : col_idx + (int64_t)row * n;
