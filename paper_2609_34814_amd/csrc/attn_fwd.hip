@@ -224,9 +224,9 @@ __device__ __forceinline__ Args kernel_args() {
 }
 
 // What a workgroup computes next: chunk `chunk` of the `chunks` chunks of a row's list (1: the whole
-// row), list entries [beg, end).
+// row), list entries [beg, end) of a list that starts at entry `list`.
 struct Task {
-  int32_t bh, row, beg, end, chunks, chunk, tile;
+  int32_t bh, row, list, beg, end, chunks, chunk, tile;
 };
 
 // The first task of workgroup b is fixed: the chunks of the split rows go to workgroups 0, 1, ..., and the
@@ -280,7 +280,7 @@ __device__ bool queue_task(Args a, int x, int t, int longest, Task* out) {
   }
   int beg, end;
   wa::row_range(a, bh, row, &beg, &end);
-  *out = {bh, row, beg, end, 1, 0, 0};
+  *out = {bh, row, beg, beg, end, 1, 0, 0};
   return end - beg <= longest;
 }
 
@@ -289,7 +289,7 @@ __device__ void split_task(Args a, int k, Task* out) {
   int beg, end;
   wa::row_range(a, e.x, e.y, &beg, &end);
   const int n = end - beg, c = e.z & 0xFFFF, chunks = e.z >> 16;
-  *out = {e.x, e.y, beg + n * c / chunks, beg + n * (c + 1) / chunks, chunks, c, e.w};
+  *out = {e.x, e.y, beg, beg + n * c / chunks, beg + n * (c + 1) / chunks, chunks, c, e.w};
 }
 
 // Next task of this workgroup, run by one wavefront (t: its first lane's): the chunks of the split rows first
@@ -393,6 +393,7 @@ __global__ __launch_bounds__(BLK * 2, D == 64 && BLK == 64 ? 3 : 2) void attn_fw
     __syncthreads();
     const int bh = __builtin_amdgcn_readfirstlane(task.bh);
     const int row = __builtin_amdgcn_readfirstlane(task.row);
+    const int list = __builtin_amdgcn_readfirstlane(task.list);  // the row's first entry
     const int beg = __builtin_amdgcn_readfirstlane(task.beg);
     const int end = __builtin_amdgcn_readfirstlane(task.end);
     const int chunks = __builtin_amdgcn_readfirstlane(task.chunks);
@@ -565,53 +566,61 @@ __global__ __launch_bounds__(BLK * 2, D == 64 && BLK == 64 ? 3 : 2) void attn_fw
     const bool ragged_last = end > beg && (n % BLK) != 0 && cols[end - 1] == mb - 1;
     const int e_plain = end - (ragged_last ? 1 : 0);
 
-    // Pass 0 takes the first block's maximum as the reference. If some probability reached
+    // Pass 0 takes the maximum of the row's first block as the reference. If some probability reached
     // kProbLimit (a later score above the reference by log2(kProbLimit) or more, in log2 units), the
     // whole workgroup recomputes the row: the exact row maximum over all its blocks first, then
     // pass 1 against it (every probability <= 1). The decision is per workgroup, since its wavefronts
-    // share the tile copies.
-    for (int pass = 0;; ++pass) {
-      if (beg < end) {
-        j_cur = cols[beg];
-        if ((unsigned)j_cur >= (unsigned)mb) {
-          j_cur = 0;
-          bad_kv = 1;
+    // share the tile copies. A later chunk of a split row computes the scores of the row's first block
+    // before pass 0 (pass -1), so its probabilities are, rounded to bf16, those of the unsplit row: against the
+    // first block of its own, O differed from the unsplit row's in a third of its values (2e-3 in the 2-norm; now 3e-4 of them) and an
+    // unnormalised chunk of small weight could overflow.
+    for (int pass = chunk > 0 ? -1 : 0;; ++pass) {
+      int m0 = list, m1 = list + 1;  // blocks of the maximum that the next pass takes as its reference
+      if (pass >= 0) {
+        if (beg < end) {
+          j_cur = cols[beg];
+          if ((unsigned)j_cur >= (unsigned)mb) {
+            j_cur = 0;
+            bad_kv = 1;
+          }
+          issue_tile<D, BLK, false>(k_lds, kg, j_cur * BLK, n, w, lane);
+          issue_vt<D, BLK>(v_lds, vtg, vt_row_bytes, j_cur * BLK, w, lane);
         }
-        issue_tile<D, BLK, false>(k_lds, kg, j_cur * BLK, n, w, lane);
-        issue_vt<D, BLK>(v_lds, vtg, vt_row_bytes, j_cur * BLK, w, lane);
-      }
-      // the Q loads (issued first) are complete; the first tiles stay in flight
-      WA_WAIT_VM(2 * C::NK);
+        // the Q loads (issued first) are complete; the first tiles stay in flight
+        WA_WAIT_VM(2 * C::NK);
 #pragma unroll
-      for (int t = 0; t < C::DT; ++t)
+        for (int t = 0; t < C::DT; ++t)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) oacc[t][v] = 0.f;
-      l_run = 0.f;
-      e = beg;
-      if (e < e_plain) {
-        if (pass == 0) {
-          kv_block(std::false_type{}, std::true_type{});
-        } else {
-          kv_block(std::false_type{}, std::false_type{});
+          for (int v = 0; v < 16; ++v) oacc[t][v] = 0.f;
+        l_run = 0.f;
+        e = beg;
+        if (e < e_plain) {
+          if (pass == 0 && chunk == 0) {
+            kv_block(std::false_type{}, std::true_type{});
+          } else {
+            kv_block(std::false_type{}, std::false_type{});
+          }
+          for (++e; e < e_plain; ++e) kv_block(std::false_type{}, std::false_type{});
+          if (ragged_last) kv_block(std::true_type{}, std::false_type{});
+        } else if (ragged_last) {
+          if (pass == 0 && chunk == 0) {
+            kv_block(std::true_type{}, std::true_type{});
+          } else {
+            kv_block(std::true_type{}, std::false_type{});
+          }
         }
-        for (++e; e < e_plain; ++e) kv_block(std::false_type{}, std::false_type{});
-        if (ragged_last) kv_block(std::true_type{}, std::false_type{});
-      } else if (ragged_last) {
-        if (pass == 0) {
-          kv_block(std::true_type{}, std::true_type{});
-        } else {
-          kv_block(std::true_type{}, std::false_type{});
-        }
+        if (pass > 0) break;
+        if (__builtin_amdgcn_ballot_w64(!(l_run < kProbLimit)) && lane == 0) redo = 1;  // also inf / NaN
+        __syncthreads();
+        const int again = __builtin_amdgcn_readfirstlane(redo);
+        __syncthreads();  // every wavefront has read the flag before the next row clears it
+        if (!again) break;
+        m0 = beg;
+        m1 = end;
       }
-      if (pass > 0) break;
-      if (__builtin_amdgcn_ballot_w64(!(l_run < kProbLimit)) && lane == 0) redo = 1;  // also inf / NaN
-      __syncthreads();
-      const int again = __builtin_amdgcn_readfirstlane(redo);
-      __syncthreads();  // every wavefront has read the flag before the next row clears it
-      if (!again) break;
-      // exact row maximum: K tiles one at a time, scores only
+      // exact maximum: K tiles one at a time, scores only
       float mx = -INFINITY;
-      for (int e2 = beg; e2 < end; ++e2) {
+      for (int e2 = m0; e2 < m1; ++e2) {
         int j = cols[e2];
         if ((unsigned)j >= (unsigned)mb) j = 0;
         issue_tile<D, BLK, false>(k_lds, kg, j * BLK, n, w, lane);
