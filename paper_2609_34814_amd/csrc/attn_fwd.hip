@@ -673,7 +673,8 @@ __global__ __launch_bounds__(BLK * 2, D == 64 && BLK == 64 ? 3 : 2) void attn_fw
       const float* first = a->part + (size_t)tile * tile_floats;
       const int qrow = BLK * D + qloc;
       // Each step reads the pieces of MC chunks together (a serial walk over the chunks costs a memory
-      // latency each); past the last chunk, the last one again with weight 0.
+      // latency each); past the last chunk the last one again, with its bits cleared (its sums may be infinite, so
+      // weight 0 is not enough; a select compiles to branches, 32.4 us instead of 31.1 for 2 x 64 rows of 64-token blocks).
       constexpr int MC = 4;
       auto at = [&](int c) { return first + (size_t)min(c, chunks - 1) * tile_floats; };
       float m = -INFINITY, l = 0.f;
@@ -706,14 +707,17 @@ __global__ __launch_bounds__(BLK * 2, D == 64 && BLK == 64 ? 3 : 2) void attn_fw
           }
 #pragma unroll
           for (int c = 0; c < MC; ++c) {
-            const float wgt = c0 + c < chunks ? __builtin_amdgcn_exp2f(um[c] - m) : 0.f;
-            l += wgt * ul[c];
+            uint32_t keep = c0 + c < chunks ? ~0u : 0u;
+            asm volatile("" : "+v"(keep));
+            auto in = [&](float x) { return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, x) & keep); };
+            const float wgt = in(__builtin_amdgcn_exp2f(um[c] - m));
+            l += wgt * in(ul[c]);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-              acc[4 * j] += wgt * u[c][j].x;
-              acc[4 * j + 1] += wgt * u[c][j].y;
-              acc[4 * j + 2] += wgt * u[c][j].z;
-              acc[4 * j + 3] += wgt * u[c][j].w;
+              acc[4 * j] += wgt * in(u[c][j].x);
+              acc[4 * j + 1] += wgt * in(u[c][j].y);
+              acc[4 * j + 2] += wgt * in(u[c][j].z);
+              acc[4 * j + 3] += wgt * in(u[c][j].w);
             }
           }
         }

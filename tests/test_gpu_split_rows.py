@@ -191,3 +191,25 @@ def test_split_rows_take_the_reference_of_the_unsplit_row(d, block):
     fin = torch.isfinite(lse[0, 0])
     assert torch.equal(fin, torch.isfinite(lse_s[0, 0]))
     assert float((lse[0, 0][fin] - lse_s[0, 0][fin]).abs().max()) <= 8 * 2.0 ** -20
+
+
+@pytest.mark.parametrize("d,block", [(64, 64), (64, 128), (128, 64), (128, 128)])
+def test_split_rows_with_infinite_values(d, block):
+    """V infinite at one token of a row's last chunk: that column of O is the infinity, the others as without it, for rows
+    of two, three and four chunks (the merge takes four at a time)."""
+    import paper_2609_34814_amd as W
+    mb, n = 41, 41 * block - 7
+    g = torch.Generator(device="cuda").manual_seed(d + block)
+    q, k, v = (torch.randn(1, 1, n, d, generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    mask = _mask(1, mb, np.random.default_rng(d + block))
+    mask[0, 0, 3:7, mb - 1] = 1       # the last block, in the last chunk
+    mask = u8_dev(mask)
+    plain = W.sparse_attn(q, k, v, mask, block=block)[0, 0]
+    v[0, 0, n - 3, 5] = float("inf")
+    v[0, 0, n - 2, d - 1] = -float("inf")
+    o = W.sparse_attn(q, k, v, mask, block=block)[0, 0]
+    for r in (3, 4, 5, 6):
+        t = slice(r * block, (r + 1) * block)
+        assert bool(torch.isposinf(o[t, 5]).all()) and bool(torch.isneginf(o[t, d - 1]).all()), r
+        rest = [c for c in range(d) if c not in (5, d - 1)]
+        assert torch.equal(o[t][:, rest], plain[t][:, rest]), r
