@@ -288,8 +288,10 @@ __device__ void split_task(Args a, int k, Task* out) {
   const int4 e = ((const int4*)(a->split + wa::kSplitHead))[k];
   int beg, end;
   wa::row_range(a, e.x, e.y, &beg, &end);
-  const int n = end - beg, c = e.z & 0xFFFF, chunks = e.z >> 16;
-  *out = {e.x, e.y, beg, beg + n * c / chunks, beg + n * (c + 1) / chunks, chunks, c, e.w};
+  // the first n mod chunks chunks are one block longer (n times c does not fit 32 bits for the longest lists)
+  const int n = end - beg, c = e.z & 0xFFFF, chunks = e.z >> 16, per = n / chunks, more = n - per * chunks;
+  const int b = beg + c * per + min(c, more);
+  *out = {e.x, e.y, beg, b, b + per + (c < more ? 1 : 0), chunks, c, e.w};
 }
 
 // Next task of this workgroup, run by one wavefront (t: its first lane's): the chunks of the split rows first

@@ -213,3 +213,26 @@ def test_split_rows_with_infinite_values(d, block):
         assert bool(torch.isposinf(o[t, 5]).all()) and bool(torch.isneginf(o[t, d - 1]).all()), r
         rest = [c for c in range(d) if c not in (5, d - 1)]
         assert torch.equal(o[t][:, rest], plain[t][:, rest]), r
+
+
+def test_chunks_of_a_list_with_repeats():
+    """A caller-built list that names every block 1,200 times (1.8 M entries, in 1,229 chunks on 256 compute units: entries
+    times chunks exceed 2^31): O is that of the plain row, the LSE larger by ln 1200."""
+    import paper_2609_34814_amd as W
+    mb, d, block, times = 1500, 64, 64, 1200
+    n = mb * block
+    g = torch.Generator(device="cuda").manual_seed(7)
+    q, k, v = (torch.randn(1, 1, n, d, generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    vt = W.transpose_v(v, block=block)
+    lists = []
+    for repeat in (1, times):
+        row_ptr = torch.zeros(1, 1, mb + 1, dtype=torch.int32, device="cuda")
+        row_ptr[0, 0, 1:] = repeat * mb
+        col_idx = torch.zeros(mb * mb, dtype=torch.int32, device="cuda")
+        col_idx[:repeat * mb] = torch.arange(mb, dtype=torch.int32, device="cuda").repeat(repeat)
+        lists.append((row_ptr, col_idx))
+    (o1, l1), (o2, l2) = (W.sparse_attn_vt(q, k, vt, *x, block=block, return_lse=True) for x in lists)
+    o1, o2 = o1[0, 0, :block].double(), o2[0, 0, :block].double()
+    # float32 sums of 1.2e8 terms, a few thousand per accumulator and chunk: below a bf16 rounding
+    assert float((o1 - o2).norm() / o1.norm()) <= 2.0 ** -8
+    assert float((l2[0, 0, :block] - l1[0, 0, :block] - np.log(times)).abs().max()) <= 1e-3
