@@ -260,8 +260,9 @@ __device__ void ilv_order(const WaAttnLaunch& a, OrderLds& L, int x) {
 }
 
 // Split plan (one workgroup): L from the kept blocks per resident workgroup, grown until the chunks of
-// the rows above it fit the tiles; then one task per chunk, enumerated over the slots (a row that no
-// slot names is not computed). Counted over the rows as well, so that L is the same for every order.
+// the rows above it fit the tiles; then one task per chunk, enumerated over the slots that a queue holds (a row
+// that no slot names, or only a slot outside every segment of the caller's table, is not computed). Counted over the
+// rows as well, so that L is the same for every order.
 __device__ void split_plan(const WaAttnLaunch& a, OrderLds& S, int slots) {
   const int t = threadIdx.x;
   if (t == 0 && a.status) *a.status = 0;
@@ -286,6 +287,15 @@ __device__ void split_plan(const WaAttnLaunch& a, OrderLds& S, int slots) {
     if (a.perm) *r = a.perm[i];
     return (unsigned)*r < (unsigned)a.mb ? blocks(*h, *r) : 0;
   };
+  auto queued = [&](int i, int h) {  // slot i - h mb lies in a segment
+    if (!a.seg) return true;
+    for (int x = 0; x < a.n_xcd; ++x) {
+      int s0, s1;
+      queue_segment(a, h, x, &s0, &s1);
+      if (s0 <= i - h * a.mb && i - h * a.mb < s1) return true;
+    }
+    return false;
+  };
   int mine = 0, total = 0;
   for (;;) {
     total = 0;
@@ -294,7 +304,7 @@ __device__ void split_plan(const WaAttnLaunch& a, OrderLds& S, int slots) {
     mine = 0;
     for (int i = t; i < rows; i += PT) {
       const int n = slot_blocks(i, &h, &r);
-      if (n > L) mine += (n + L - 1) / L;
+      if (n > L && queued(i, h)) mine += (n + L - 1) / L;
       if (a.perm) {
         const int m = blocks(h, i - h * a.mb);
         if (m > L) by_row += (m + L - 1) / L;
@@ -316,7 +326,7 @@ __device__ void split_plan(const WaAttnLaunch& a, OrderLds& S, int slots) {
   int at = mine, h, r;
   for (int i = t; i < rows; i += PT) {
     const int n = slot_blocks(i, &h, &r);
-    if (n <= L) continue;
+    if (n <= L || !queued(i, h)) continue;
     const int chunks = (n + L - 1) / L;
     a.split[wa::split_arrival(a.split_cap, at)] = 0;
     for (int c = 0; c < chunks; ++c) tasks[at + c] = make_int4(h, r, c | (chunks << 16), at);

@@ -236,3 +236,29 @@ def test_chunks_of_a_list_with_repeats():
     # float32 sums of 1.2e8 terms, a few thousand per accumulator and chunk: below a bf16 rounding
     assert float((o1 - o2).norm() / o1.norm()) <= 2.0 ** -8
     assert float((l2[0, 0, :block] - l1[0, 0, :block] - np.log(times)).abs().max()) <= 1e-3
+
+
+def test_slots_outside_the_segments_are_not_computed():
+    """A segment table that leaves slots out: their rows keep their old contents, whether they would be split or not."""
+    import paper_2609_34814_amd as W
+    mb, d, block = 41, 64, 64
+    n = mb * block
+    g = torch.Generator(device="cuda").manual_seed(5)
+    q, k, v = (torch.randn(1, 2, n, d, generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    mask = u8_dev(_mask(2, mb, np.random.default_rng(5)))
+    want = W.sparse_attn(q, k, v, mask, block=block)
+    # head 0 runs slots 3 to 5 alone (slot 6, the full row, is left out); head 1 all
+    seg = torch.tensor([[[3, 4, 4, 6, 6], [0, 10, 20, 30, mb]]], dtype=torch.int32, device="cuda")
+    run = torch.ones(2, mb, dtype=torch.bool)
+    run[0] = False
+    for lo, hi in zip(seg[0, 0, :-1].tolist(), seg[0, 0, 1:].tolist()):
+        run[0, lo:max(lo, hi)] = True
+    out = torch.full_like(want, float("nan"))
+    W.sparse_attn(q, k, v, mask, None, seg, block=block, n_xcd=4, out=out)
+    for h in range(2):
+        for r in range(mb):
+            t = slice(r * block, (r + 1) * block)
+            if run[h, r]:
+                assert torch.equal(out[0, h, t], want[0, h, t]), (h, r)
+            else:
+                assert bool(torch.isnan(out[0, h, t]).all()), (h, r)
