@@ -218,16 +218,21 @@ wa_status wa_produce_block_mask(const void* q, const void* k, const wa_shape* sh
  * must not overlap. */
 wa_status wa_mask_producer_workspace_size(const wa_shape* shape, size_t* bytes);
 
-/* Workspace bytes needed by wa_sparse_attn: the scheduler state (the
+/* Workspace bytes needed by wa_sparse_attn: the scheduler state (queue counters,
  * per-queue prefix tables and the per-queue order of the last heads: 64 + 64 * (B*H + 1)
  * int32 rounded up to 64 entries, plus 64 * T * M_B int32 with T = min(B*H, 16384 / M_B, 256)
  * rounded up to 64 entries, plus 64 + B*H*M_B int32 for the head-interleaved order,
- * rounded up to 256 bytes), the task counters (8.25 KiB) with the state of split rows (launches of up to
- * 2^22 / block query blocks: at most 32 MiB of float32 tiles, their tasks and counters),
+ * rounded up to 256 bytes),
  * a zero-padded transposed copy of V (bf16 [B][H][head_dim][M_B*block], rounded up
- * to 256 bytes), then the compacted lists. The parts before the lists
+ * to 256 bytes), then the compacted lists. The first two parts (the leading part)
  * suffice for wa_sparse_attn_csr. Calls that share a workspace must not overlap. */
 wa_status wa_attn_workspace_size(const wa_shape* shape, size_t* bytes);
+
+/* Bytes by which a workspace of wa_sparse_attn, _csr or _vt must exceed what the call needs for
+ * rows to be split (see wa_sparse_attn): the chunks' tasks, counters and at most 32 MiB of
+ * float32 tiles; 0 for launches that split none (more than 2^22 / block query blocks, or at most 12
+ * per head). A smaller workspace is as valid: the call then computes every row whole. */
+wa_status wa_attn_split_workspace_size(const wa_shape* shape, size_t* bytes);
 
 /* Status word of the attention calls (device int32, nullable): zeroed by the call, then
  * bits are set for what the call found. An invalid perm entry (outside 0..M_B-1)
@@ -262,7 +267,8 @@ enum { WA_ATTN_BAD_PERM = 1, WA_ATTN_BAD_KV_INDEX = 2 };
  *                block count times the queue's share of workgroups exceeds the blocks
  *                queued after it) is taken first, longest first; the others keep their
  *                order. The order changes when rows run, never what they compute.
- *                In a launch of few rows, a row of more than L kept blocks is computed in chunks
+ *                In a launch of few rows whose workspace has the room (wa_attn_split_workspace_size),
+ *                a row of more than L kept blocks is computed in chunks
  *                of at most L by several workgroups and merged in chunk order; L follows from
  *                the lists and the device alone, so O is still the same for every order.
  *   o            out bf16 [B][H][N][d]
@@ -276,7 +282,7 @@ wa_status wa_sparse_attn(const void* q, const void* k, const void* v, const uint
 
 /* As wa_sparse_attn, from lists already built by wa_compact_mask (row i of head
  * (b,h) visits col_idx[(b*H+h)*M_B*N_B + row_ptr[b][h][i] ...] in list order).
- * workspace >= the scheduler, split-row and V^T parts of wa_attn_workspace_size, 256-byte aligned. */
+ * workspace >= the scheduler and V^T parts of wa_attn_workspace_size, 256-byte aligned. */
 wa_status wa_sparse_attn_csr(const void* q, const void* k, const void* v, const int32_t* row_ptr,
                              const int32_t* col_idx, const int32_t* perm, const int32_t* seg_start,
                              const wa_shape* shape,
@@ -307,7 +313,7 @@ typedef struct wa_attn_options {
   int32_t head_order;   /* WA_HEADS_IN_ORDER or WA_HEADS_INTERLEAVED */
 } wa_attn_options;
 
-/* Workspace bytes needed by wa_sparse_attn_vt: the scheduler and split-row state of
+/* Workspace bytes needed by wa_sparse_attn_vt: the scheduler state of
  * wa_attn_workspace_size alone. */
 wa_status wa_attn_vt_workspace_size(const wa_shape* shape, size_t* bytes);
 
@@ -325,10 +331,10 @@ wa_status wa_sparse_attn_vt(const void* q, const void* k, const void* vt, const 
 
 /* For callers that cannot allocate device memory: code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc. The same computation as
- * wa_sparse_attn_vt, with the scheduler state (prefix tables, the
+ * wa_sparse_attn_vt, with the scheduler state (queue counters, prefix tables, the
  * orders of the last heads and the head-interleaved table) kept in a static device
  * array of the library instead of a workspace: WA_NOALLOC_SCRATCH_BYTES per GPU (and
- * 32.25 MiB for the task counters and the state of split rows), taken when the library's code is loaded on
+ * 32.25 MiB for the state of split rows), taken when the library's code is loaded on
  * that GPU and held until the process ends. The call allocates and frees nothing. A shape whose state needs more
  * (64 + n_xcd*(B*H+1) rounded up to 64, + n_xcd*T*M_B rounded up to 64, + 64 + B*H*M_B
  * int32, T as for wa_attn_workspace_size) is rejected with WA_ERR_WORKSPACE before

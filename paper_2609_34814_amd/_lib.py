@@ -68,6 +68,7 @@ _SIGNATURES = {
     "wa_produce_block_mask": (c_int32, [c_void_p, c_void_p, POINTER(WaShape), c_int32, c_int32, c_void_p, c_void_p,
                                         c_void_p, c_void_p, c_size_t, c_void_p]),
     "wa_attn_workspace_size": (c_int32, [POINTER(WaShape), POINTER(c_size_t)]),
+    "wa_attn_split_workspace_size": (c_int32, [POINTER(WaShape), POINTER(c_size_t)]),
     "wa_sparse_attn": (c_int32, [c_void_p, c_void_p, c_void_p, c_void_p, c_void_p, c_void_p, POINTER(WaShape),
                                  c_float, c_int32, c_void_p, c_void_p, c_void_p, c_void_p, c_size_t, c_void_p]),
     "wa_sparse_attn_csr": (c_int32, [c_void_p, c_void_p, c_void_p, c_void_p, c_void_p, c_void_p, c_void_p,

@@ -99,11 +99,23 @@ def perm_workspace_size(shape: L.WaShape) -> int:
     return n.value
 
 
-def attn_workspace_size(shape: L.WaShape) -> int:
-    lib = L.load()
+def _size(call: str, shape: L.WaShape) -> int:
     n = ctypes.c_size_t(0)
-    L.check(lib.wa_attn_workspace_size(ctypes.byref(shape), ctypes.byref(n)))
+    L.check(getattr(L.load(), call)(ctypes.byref(shape), ctypes.byref(n)))
     return n.value
+
+
+def _attn_workspace(workspace, call: str, shape: L.WaShape, device) -> torch.Tensor:
+    """The given workspace if the call can run in it, else a new one with room for split rows."""
+    need = _size(call, shape)
+    if workspace is None or workspace.numel() < need:
+        workspace = _workspace(need + _size("wa_attn_split_workspace_size", shape), device)
+    return workspace
+
+
+def attn_workspace_size(shape: L.WaShape) -> int:
+    """Bytes for sparse_attn and sparse_attn_csr, with the room in which rows can be split."""
+    return _size("wa_attn_workspace_size", shape) + _size("wa_attn_split_workspace_size", shape)
 
 
 def mask_stats(mask: torch.Tensor, *, seq_len: int, block: int, head_dim: int = 128):
@@ -300,9 +312,7 @@ def sparse_attn(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, mask: torch.T
     _check(workspace, "workspace", torch.uint8)
     o, lse = _attn_outputs(q, out, status, return_lse)
     _on_device(q=q, k=k, v=v, mask=mask, perm=perm, seg=seg, out=o, status=status, workspace=workspace)
-    need = attn_workspace_size(shape)
-    if workspace is None or workspace.numel() < need:
-        workspace = _workspace(need, q.device)
+    workspace = _attn_workspace(workspace, "wa_attn_workspace_size", shape, q.device)
     L.check(lib.wa_sparse_attn(_ptr(q), _ptr(k), _ptr(v), _ptr(mask), _ptr(perm), _ptr(seg), ctypes.byref(shape),
                                float(scale or 0.0), int(n_xcd), _ptr(o), _ptr(lse), _ptr(status), _ptr(workspace),
                                workspace.numel(), _stream()))
@@ -321,9 +331,7 @@ def sparse_attn_csr(q, k, v, row_ptr, col_idx, perm=None, seg=None, *, block: in
     o, lse = _attn_outputs(q, out, status, return_lse)
     _on_device(q=q, k=k, v=v, row_ptr=row_ptr, col_idx=col_idx, perm=perm, seg=seg, out=o, status=status,
                workspace=workspace)
-    need = attn_workspace_size(shape)
-    if workspace is None or workspace.numel() < need:
-        workspace = _workspace(need, q.device)
+    workspace = _attn_workspace(workspace, "wa_attn_workspace_size", shape, q.device)
     L.check(lib.wa_sparse_attn_csr(_ptr(q), _ptr(k), _ptr(v), _ptr(row_ptr), _ptr(col_idx), _ptr(perm), _ptr(seg),
                                    ctypes.byref(shape), float(scale or 0.0), int(n_xcd), _ptr(o), _ptr(lse),
                                    _ptr(status), _ptr(workspace), workspace.numel(), _stream()))
@@ -346,10 +354,8 @@ def transpose_v(v: torch.Tensor, *, block: int, out: Optional[torch.Tensor] = No
 
 
 def attn_vt_workspace_size(shape: L.WaShape) -> int:
-    lib = L.load()
-    n = ctypes.c_size_t(0)
-    L.check(lib.wa_attn_vt_workspace_size(ctypes.byref(shape), ctypes.byref(n)))
-    return n.value
+    """Bytes for sparse_attn_vt, with the room in which rows can be split."""
+    return _size("wa_attn_vt_workspace_size", shape) + _size("wa_attn_split_workspace_size", shape)
 
 
 def sparse_attn_vt(q, k, vt, row_ptr, col_idx, perm=None, seg=None, *, block: int, scale: Optional[float] = None,
@@ -368,9 +374,7 @@ def sparse_attn_vt(q, k, vt, row_ptr, col_idx, perm=None, seg=None, *, block: in
     o, lse = _attn_outputs(q, out, status, return_lse)
     _on_device(q=q, k=k, vt=vt, row_ptr=row_ptr, col_idx=col_idx, perm=perm, seg=seg, out=o, status=status,
                workspace=workspace)
-    need = attn_vt_workspace_size(shape)
-    if workspace is None or workspace.numel() < need:
-        workspace = _workspace(need, q.device)
+    workspace = _attn_workspace(workspace, "wa_attn_vt_workspace_size", shape, q.device)
     opts = L.WaAttnOptions(float(scale or 0.0), int(n_xcd), _HEAD_ORDER[head_order])
     L.check(lib.wa_sparse_attn_vt(_ptr(q), _ptr(k), _ptr(vt), _ptr(row_ptr), _ptr(col_idx), _ptr(perm), _ptr(seg),
                                   ctypes.byref(shape), ctypes.byref(opts), _ptr(o), _ptr(lse), _ptr(status),

@@ -122,15 +122,18 @@ void perm_ws_pointers(WaPermLaunch& a, const PermWs& L, char* base) {
   a.stats = (PermStats*)(base + L.stats);
 }
 
-// Attention workspace: [scheduler state][task counters and split rows][V^T copy][row_ptr][col_idx]; the CSR entry point
-// uses the first three parts, the V^T one the first two. The scheduler part is sized for the largest n_xcd.
+// Attention workspace: [scheduler state][V^T copy][row_ptr][col_idx]; the CSR entry point needs the first two
+// parts, the V^T one the first. The scheduler part is sized for the largest n_xcd. A larger workspace may hold the
+// split rows behind the parts that the call needs; without that room no row is split.
 constexpr int kMaxXcd = 64;
-size_t attn_order_bytes(const Dims& d) { return align_up(wa::sched_state_ints(d.bh, d.mb, kMaxXcd) * 4); }
+size_t attn_sched_bytes(const Dims& d) { return align_up(wa::sched_state_ints(d.bh, d.mb, kMaxXcd) * 4); }
 size_t attn_split_bytes(const Dims& d) {
   const int cap = wa::split_cap(d.bh, d.mb, d.blk, d.d);
-  return align_up(wa::split_ints(cap) * 4 + cap * wa::part_tile_floats(d.blk, d.d) * 4);
+  return cap > 0 ? align_up(wa::split_ints(cap) * 4 + cap * wa::part_tile_floats(d.blk, d.d) * 4) : 0;
 }
-size_t attn_sched_bytes(const Dims& d) { return attn_order_bytes(d) + attn_split_bytes(d); }
+void* split_part(void* ws, size_t have, size_t need, const Dims& d) {
+  return have - need >= attn_split_bytes(d) ? (char*)ws + need : nullptr;
+}
 size_t attn_csr_ws_bytes(const Dims& d) {
   return attn_sched_bytes(d) + align_up(wa_vt_bytes(d.bh, d.mb, d.d, d.blk));
 }
@@ -181,8 +184,8 @@ wa_status launch_compact(const uint8_t* mask, const Dims& d, int32_t* row_ptr, i
 
 // v: V in its natural layout (transposed into the workspace after the scheduler state), or null with
 // vt: V already transposed by the caller. The lists come packed (row_ptr) or at a fixed stride (row_cnt).
-// split: the task counters and the split rows' memory, attn_split_bytes(d).
-wa_status launch_attn(const void* q, const void* k, const void* v, const void* vt, void* ws, void* split,
+// ws: the scheduler state, sched_bytes of it; split: attn_split_bytes(d), or null.
+wa_status launch_attn(const void* q, const void* k, const void* v, const void* vt, void* ws, size_t sched_bytes, void* split,
                       const int32_t* row_ptr, const int32_t* row_cnt, const int32_t* col_idx, const int32_t* perm,
                       const int32_t* seg, const Dims& d, float scale, int32_t n_xcd, int32_t head_order, void* o,
                       float* lse, int32_t* status, hipStream_t st) {
@@ -190,9 +193,12 @@ wa_status launch_attn(const void* q, const void* k, const void* v, const void* v
   a.q = q; a.k = k; a.v = v;
   a.sched = (int32_t*)ws;
   a.vt = v ? (void*)((char*)ws + attn_sched_bytes(d)) : const_cast<void*>(vt);
-  a.split_cap = wa::split_cap(d.bh, d.mb, d.blk, d.d);
-  a.split = (int32_t*)split;
-  a.part = (float*)(a.split + wa::split_ints(a.split_cap));
+  wa::spread_counters(a.sched, sched_bytes / 4, d.bh, d.mb, n_xcd, &a.counters, &a.counter_step);
+  a.split_cap = split ? wa::split_cap(d.bh, d.mb, d.blk, d.d) : 0;
+  if (a.split_cap > 0) {
+    a.split = (int32_t*)split;
+    a.part = (float*)(a.split + wa::split_ints(a.split_cap));
+  }
   a.row_ptr = row_ptr; a.row_cnt = row_cnt; a.col_idx = col_idx; a.perm = perm; a.seg = seg;
   a.o = o; a.lse = lse; a.status = status; a.head_order = head_order;
   a.bh = (int32_t)d.bh; a.seq_len = d.n; a.mb = d.mb; a.head_dim = d.d; a.block = d.blk; a.n_xcd = n_xcd;
@@ -424,6 +430,15 @@ wa_status wa_attn_workspace_size(const wa_shape* shape, size_t* bytes) {
   return ok();
 }
 
+wa_status wa_attn_split_workspace_size(const wa_shape* shape, size_t* bytes) {
+  Dims d;
+  wa_status s = check_shape(shape, &d);
+  if (s != WA_OK) return s;
+  if (!bytes) return fail(WA_ERR_INVALID_ARG, "bytes is null");
+  *bytes = attn_split_bytes(d);
+  return ok();
+}
+
 wa_status wa_sparse_attn(const void* q, const void* k, const void* v, const uint8_t* mask, const int32_t* perm,
                          const int32_t* seg_start, const wa_shape* shape, float softmax_scale, int32_t n_xcd,
                          void* o, float* lse, int32_t* status, void* workspace, size_t workspace_bytes,
@@ -443,7 +458,7 @@ wa_status wa_sparse_attn(const void* q, const void* k, const void* v, const uint
   // lists at a fixed stride: one pass over the mask, where packed ones take a count, a scan and a second pass
   hipError_t e = wa_launch_row_write(mask, (int)d.bh, d.mb, d.mb, nullptr, row_cnt, col_idx, st);
   if (e != hipSuccess) return hip_fail(e, "row_write launch");
-  s = launch_attn(q, k, v, nullptr, base, base + attn_order_bytes(d), nullptr, row_cnt, col_idx, perm, seg_start,
+  s = launch_attn(q, k, v, nullptr, base, attn_sched_bytes(d), split_part(base, workspace_bytes, attn_ws_bytes(d), d), nullptr, row_cnt, col_idx, perm, seg_start,
                   d, softmax_scale, n_xcd, 0, o, lse, status, st);
   if (s != WA_OK) return s;
   return ok();
@@ -462,8 +477,8 @@ wa_status wa_sparse_attn_csr(const void* q, const void* k, const void* v, const 
   if (!row_ptr || !col_idx) return fail(WA_ERR_INVALID_ARG, "row_ptr and col_idx must be non-null");
   s = check_ws(workspace, workspace_bytes, attn_csr_ws_bytes(d));
   if (s != WA_OK) return s;
-  s = launch_attn(q, k, v, nullptr, workspace, (char*)workspace + attn_order_bytes(d), row_ptr, nullptr, col_idx, perm,
-                  seg_start, d, softmax_scale, n_xcd, 0, o, lse, status, (hipStream_t)stream);
+  s = launch_attn(q, k, v, nullptr, workspace, attn_sched_bytes(d),
+                  split_part(workspace, workspace_bytes, attn_csr_ws_bytes(d), d), row_ptr, nullptr, col_idx, perm, seg_start, d, softmax_scale, n_xcd, 0, o, lse, status, (hipStream_t)stream);
   if (s != WA_OK) return s;
   return ok();
 }
@@ -494,7 +509,7 @@ wa_status wa_sparse_attn_vt_noalloc(const void* q, const void* k, const void* vt
   if (need > have || attn_split_bytes(d) > have_split)
     return fail(WA_ERR_WORKSPACE, "static scratch holds %zu + %zu bytes, %zu + %zu needed", have, have_split, need,
                 attn_split_bytes(d));
-  s = launch_attn(q, k, nullptr, vt, scratch, split, row_ptr, nullptr, col_idx, perm, seg_start, d,
+  s = launch_attn(q, k, nullptr, vt, scratch, have, attn_split_bytes(d) > 0 ? split : nullptr, row_ptr, nullptr, col_idx, perm, seg_start, d,
                   options->softmax_scale, options->n_xcd, options->head_order, o, lse, status, (hipStream_t)stream);
   if (s != WA_OK) return s;
   return ok();
@@ -535,8 +550,8 @@ wa_status wa_sparse_attn_vt(const void* q, const void* k, const void* vt, const 
   if (!row_ptr || !col_idx) return fail(WA_ERR_INVALID_ARG, "row_ptr and col_idx must be non-null");
   s = check_ws(workspace, workspace_bytes, attn_sched_bytes(d));
   if (s != WA_OK) return s;
-  s = launch_attn(q, k, nullptr, vt, workspace, (char*)workspace + attn_order_bytes(d), row_ptr, nullptr, col_idx, perm,
-                  seg_start, d, options->softmax_scale, options->n_xcd, options->head_order, o, lse, status,
+  s = launch_attn(q, k, nullptr, vt, workspace, attn_sched_bytes(d),
+                  split_part(workspace, workspace_bytes, attn_sched_bytes(d), d), row_ptr, nullptr, col_idx, perm, seg_start, d, options->softmax_scale, options->n_xcd, options->head_order, o, lse, status,
                   (hipStream_t)stream);
   if (s != WA_OK) return s;
   return ok();

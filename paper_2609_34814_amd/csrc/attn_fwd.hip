@@ -338,14 +338,14 @@ __device__ void fetch_task(Args a, bool first, Task* t) {
   for (;;) {
     // queues with entries left; a counter only grows, so the loop ends when every queue is drained
     bool left = given < total;
-    if (left) left = given + __hip_atomic_load(a->split + wa::queue_counter(lane, a->n_xcd), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < total;
+    if (left) left = given + __hip_atomic_load(a->counters + lane * a->counter_step, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < total;
     const uint64_t mask = __ballot(left);
     if (mask == 0) break;
     const uint64_t from_home = mask >> home << home;
     const int x = __ffsll((unsigned long long)(from_home ? from_home : mask)) - 1;
     const int x_given = __shfl(given, x), x_total = __shfl(total, x);
     if (lane == 0) {
-      const int k = x_given + atomicAdd(a->split + wa::queue_counter(x, a->n_xcd), 1);
+      const int k = x_given + atomicAdd(a->counters + x * a->counter_step, 1);
       got = k < x_total && queue_task(a, x, k, longest, t);
     }
     if (__ballot(got)) return;

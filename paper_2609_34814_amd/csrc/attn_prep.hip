@@ -63,7 +63,7 @@ __device__ void queue_prefix(const WaAttnLaunch& a, OrderLds& L, int x) {
   const int t = threadIdx.x;
   int32_t* px = a.sched + 64 + (int64_t)x * (a.bh + 1);
   if (t == 0) {
-    a.split[wa::queue_counter(x, a.n_xcd)] = 0;
+    a.counters[x * a.counter_step] = 0;
     px[0] = 0;
   }
   int carry = 0;

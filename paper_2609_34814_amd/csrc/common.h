@@ -28,9 +28,9 @@ __host__ __device__ inline void xcd_segment(int x, int m, int n_xcd, const int32
 // the tail order, so fixed per shape rather than following the kernel's occupancy as it changes.
 __host__ __device__ constexpr int wave_wgs(int d, int block) { return block == 128 ? 2 : d == 128 ? 4 : 6; }
 
-// Scheduler state of one attention call, in the caller's workspace: per queue (queue x holds segment x of
-// every head, heads in order), from 64, the prefix sums of its segment lengths over the heads. The first 64
-// int32 are not used.
+// Scheduler state of one attention call, in the caller's workspace: a task counter per queue (queue x holds segment x of
+// every head, heads in order; see spread_counters) and, per queue, from 64, the prefix sums of its segment lengths
+// over the heads.
 __host__ __device__ inline size_t sched_ints(int64_t bh, int n_xcd) { return 64 + (size_t)n_xcd * (bh + 1); }
 
 // The last tail_heads(bh, m) heads of every queue run in an order built at each call (the tail
@@ -54,6 +54,19 @@ __host__ __device__ inline size_t sched_state_ints(int64_t bh, int m, int n_xcd)
   return ilv_offset(bh, m, n_xcd) + 64 + (size_t)(bh > 0 ? bh : 0) * (m > 0 ? m : 0);
 }
 
+// The task counters: spread evenly over kCounterInts int32 behind the state where the memory has room for them (it does
+// in a workspace, which is sized for 64 queues, but for the smallest calls with many queues), else the first 64
+// int32. Atomics on one line serialise across the device, and a launch takes thousands. Eight counters in 32
+// bytes, 32 bytes apart and 512 bytes apart: 70 x 83 rows (d 128) 454, 383 and 366 us, 20 x 338 rows of 64-token
+// blocks (d 128) 648, 556 and 515 us.
+constexpr int kCounterInts = 1024;
+inline void spread_counters(int32_t* sched, size_t have_ints, int64_t bh, int m, int n_xcd, int32_t** counters, int32_t* step) {
+  const size_t end = (sched_state_ints(bh, m, n_xcd) + 63) / 64 * 64;
+  const bool room = end + kCounterInts <= have_ints;
+  *counters = room ? sched + end : sched;
+  *step = room ? kCounterInts / n_xcd : 1;
+}
+
 // Split rows. A launch with few rows ends when its longest row does, so a row of more than L kept
 // blocks is computed in chunks by several workgroups: each chunk leaves its unnormalised O, row
 // maxima and row sums in a float32 tile, and the workgroup that finishes a row's last chunk merges the
@@ -74,17 +87,12 @@ __host__ __device__ inline int split_cap(int64_t bh, int m, int block, int d) {
   const int64_t most = bh * m * ((m + kSplitMinBlocks - 1) / kSplitMinBlocks);
   return (int)(most < cap ? most : cap);
 }
-// Split state: [0] chunk tasks, [1] L; the counters of tasks taken, one per queue and one per shard of the
-// chunks; from kSplitHead the tasks {head, row, chunk | chunks << 16, the row's first tile}; then one arrival
-// counter per tile (the row's first tile counts the row), 64 bytes apart. The counters of tasks have
-// 4 KiB each for the queues and the shards, spread evenly: atomics on one line serialise across the device, and a
-// launch takes thousands. Eight queue counters in 32 bytes, 32 bytes apart and 512 bytes apart:
-// 70 x 83 rows (d 128) 454, 383 and 366 us, 20 x 338 rows of 64-token blocks (d 128) 648, 556 and 515 us.
+// Split state: [0] chunk tasks, [1] L; the counters of chunks taken, one per shard of them, spread as the queues' are;
+// from kSplitHead the tasks {head, row, chunk | chunks << 16, the row's first tile}; then one arrival
+// counter per tile (the row's first tile counts the row), 64 bytes apart.
 constexpr int kSplitShards = 8;
-constexpr int kCounterInts = 1024;
-constexpr int kSplitHead = 64 + 2 * kCounterInts;
-__host__ __device__ inline int queue_counter(int x, int n_xcd) { return 64 + x * (kCounterInts / n_xcd); }
-__host__ __device__ inline int split_counter(int shard) { return 64 + kCounterInts + shard * (kCounterInts / kSplitShards); }
+constexpr int kSplitHead = 64 + kCounterInts;
+__host__ __device__ inline int split_counter(int shard) { return 64 + shard * (kCounterInts / kSplitShards); }
 __host__ __device__ inline size_t split_arrival(int cap, int tile) { return kSplitHead + 4 * (size_t)cap + 16 * (size_t)tile; }
 __host__ __device__ inline size_t split_ints(int cap) { return (split_arrival(cap, cap) + 63) / 64 * 64; }
 
@@ -117,9 +125,11 @@ struct WaAttnLaunch {
                      // workspace copy that the launch writes from v
   int32_t* sched;    // workspace: sched_state_ints(bh, mb, n_xcd) int32 (prefix tables at 64, the tail order
                      // table at tail_offset(bh, n_xcd))
-  int32_t* split;    // workspace: split_ints(split_cap) int32 (also with split_cap 0), then the tiles
+  int32_t* counters;      // queue x's task counter at counters[x * counter_step]
+  int32_t counter_step;
+  int32_t split_cap;      // 0: no row is split
+  int32_t* split;    // workspace: split_ints(split_cap) int32, then the tiles
   float* part;       // workspace: split_cap tiles of part_tile_floats(block, head_dim)
-  int32_t split_cap;
   const int32_t* row_ptr;  // [bh][mb+1], row r's list at col_idx + head mb^2 + row_ptr[r]; null:
   const int32_t* row_cnt;  // [bh][mb], row r's list at col_idx + head mb^2 + r mb
   const int32_t* col_idx;

@@ -363,3 +363,26 @@ def test_noalloc_rejects_state_beyond_its_static_scratch():
     assert lib.wa_sparse_attn_vt_noalloc(FAKE, FAKE, FAKE, FAKE, FAKE, None, None, ctypes.byref(s), None, FAKE,
                                          None, None, None) == L.WA_ERR_INVALID_ARG
     assert L.WA_NOALLOC_SCRATCH_BYTES == 4 * 1024 * 1024
+
+
+def test_attention_workspaces_keep_their_size():
+    """The sizes that the calls ask for are those of the scheduler state, the copy of V and the lists, without the room
+    for split rows (at most 32 MiB of tiles), which a larger workspace gives by itself."""
+    lib = _lib()
+
+    def up(x, a):
+        return -(-x // a) * a
+
+    n = ctypes.c_size_t(0)
+    for b, h, mb, d, blk in ((1, 2, 64, 64, 64), (2, 4, 61, 128, 128), (1, 1, 1, 64, 64), (1, 40, 2841, 128, 128)):
+        s, bh = L.WaShape(b, h, mb * blk, d, blk), b * h
+        t = min(bh, 16384 // mb, 256)
+        sched = up(4 * (up(up(64 + 64 * (bh + 1), 64) + 64 * t * mb, 64) + 64 + bh * mb), 256)
+        vt = up(2 * bh * d * mb * blk, 256)
+        assert lib.wa_attn_vt_workspace_size(ctypes.byref(s), ctypes.byref(n)) == 0 and n.value == sched
+        assert lib.wa_attn_workspace_size(ctypes.byref(s), ctypes.byref(n)) == 0
+        assert n.value == sched + vt + up(4 * bh * (mb + 1), 256) + up(4 * bh * mb * mb, 256)
+        assert lib.wa_attn_split_workspace_size(ctypes.byref(s), ctypes.byref(n)) == 0
+        assert n.value <= 33 * 2 ** 20 and (n.value == 0) == (mb <= 12 or bh * mb * blk > 2 ** 22)
+    assert lib.wa_attn_split_workspace_size(None, ctypes.byref(n)) == L.WA_ERR_INVALID_ARG
+    assert lib.wa_attn_split_workspace_size(ctypes.byref(_shape()), None) == L.WA_ERR_INVALID_ARG

@@ -262,3 +262,30 @@ def test_slots_outside_the_segments_are_not_computed():
                 assert torch.equal(out[0, h, t], want[0, h, t]), (h, r)
             else:
                 assert bool(torch.isnan(out[0, h, t]).all()), (h, r)
+
+
+@pytest.mark.parametrize("n_xcd,heads,mb", [(8, 2, 41), (64, 1, 41), (64, 1, 2)])
+def test_workspace_without_room_for_split_rows(n_xcd, heads, mb):
+    """The sizes that the C calls report: every row whole, within a bf16 rounding of the split rows in a larger one.
+    With 64 queues and few rows the task counters lie side by side."""
+    import ctypes
+    import paper_2609_34814_amd as W
+    from paper_2609_34814_amd import _lib as L
+    lib, d, block = L.load(), 64, 64
+    n = mb * block
+    g = torch.Generator(device="cuda").manual_seed(mb)
+    q, k, v = (torch.randn(1, heads, n, d, generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    mask = u8_dev(_mask(heads, mb, np.random.default_rng(mb)) if mb > 8 else np.ones((1, heads, mb, mb), np.uint8))
+    want = W.sparse_attn(q, k, v, mask, block=block, n_xcd=n_xcd)
+    rp, ci = W.compact_mask(mask, seq_len=n, block=block, head_dim=d)
+    vt = W.transpose_v(v, block=block)
+    shape, size = W.shape_of(1, heads, n, d, block), ctypes.c_size_t(0)
+    for call, run in (("wa_attn_workspace_size", lambda **kw: W.sparse_attn(q, k, v, mask, **kw)),
+                      ("wa_attn_workspace_size", lambda **kw: W.sparse_attn_csr(q, k, v, rp, ci, **kw)),
+                      ("wa_attn_vt_workspace_size", lambda **kw: W.sparse_attn_vt(q, k, vt, rp, ci, **kw))):
+        assert getattr(lib, call)(ctypes.byref(shape), ctypes.byref(size)) == 0
+        buf = torch.full((size.value + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+        out = torch.full_like(want, float("nan"))
+        run(block=block, n_xcd=n_xcd, out=out, workspace=buf[:size.value])
+        assert bool((buf[size.value:] == 0x5A).all())
+        assert float((out.float() - want.float()).norm() / want.float().norm()) <= 2e-4
