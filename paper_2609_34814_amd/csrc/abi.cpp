@@ -89,7 +89,7 @@ ProducerWs producer_ws_layout(const Dims& d) {
 }
 
 struct PermWs {
-  size_t rowbits, colbits, row_nnz, col_cnt, xg, ym, z, state, adj, stats, total;
+  size_t rowbits, colbits, row_nnz, col_cnt, head_stats, xg, ym, z, state, adj, stats, total;
 };
 
 PermWs perm_ws_layout(const Dims& d) {
@@ -100,13 +100,17 @@ PermWs perm_ws_layout(const Dims& d) {
   w.colbits = off; off = align_up(off + (size_t)d.bh * d.mb * words * 8);
   w.row_nnz = off; off = align_up(off + (size_t)d.bh * d.mb * 4);
   w.col_cnt = off; off = align_up(off + (size_t)d.bh * d.mb * 4);
+  w.head_stats = off; off = align_up(off + (size_t)d.bh * sizeof(PermStats));
   w.xg = off; off = align_up(off + (size_t)d.bh * d.mb * 2 * 4);
   w.ym = off; off = align_up(off + (size_t)d.bh * d.mb * 2 * 8);
   w.z = off; off = align_up(off + (size_t)d.bh * d.mb * 2 * 8);
   w.state = off; off = align_up(off + (size_t)d.bh * sizeof(PermState));
-  w.adj = off; off = align_up(off + (size_t)d.bh * words * sizeof(int2));
-  w.stats = off; off = align_up(off + (size_t)d.bh * wa_perm_stat_runs(d.mb) * sizeof(PermStats));
   w.total = off;
+  // The overlaps and the statistics of several runs a head lie where X will: the first scatter (or the statistics
+  // alone) has read them before the last gather, at the earliest the second, writes X. They fit: 8 bytes per 64
+  // rows and 48 per 256 columns, of 8 a row.
+  w.adj = w.xg;
+  w.stats = wa_perm_stat_runs(d.mb) == 1 ? w.head_stats : align_up(w.adj + (size_t)d.bh * words * sizeof(int2));
   return w;
 }
 

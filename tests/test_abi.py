@@ -386,3 +386,23 @@ def test_attention_workspaces_keep_their_size():
         assert n.value <= 33 * 2 ** 20 and (n.value == 0) == (mb <= 12 or bh * mb * blk > 2 ** 22)
     assert lib.wa_attn_split_workspace_size(None, ctypes.byref(n)) == L.WA_ERR_INVALID_ARG
     assert lib.wa_attn_split_workspace_size(ctypes.byref(_shape()), None) == L.WA_ERR_INVALID_ARG
+
+
+def test_permutation_workspace_keeps_its_size():
+    """Bit masks, counts, head statistics, X, the two products and the state; the overlaps and run statistics lie in the
+    room of X, which holds them for every size (checked for one head, the tightest: 256-byte pieces)."""
+    lib = _lib()
+
+    def up(x):
+        return -(-x // 256) * 256
+
+    n = ctypes.c_size_t(0)
+    for heads, mb in [(1, m) for m in range(1, 4097)] + [(3, 257), (40, 2841), (128, 4095)]:
+        s, w = L.WaShape(1, heads, mb * 64, 64, 64), -(-mb // 64)
+        assert lib.wa_perm_workspace_size(ctypes.byref(s), ctypes.byref(n)) == 0
+        want = (2 * up(8 * heads * mb * w) + 2 * up(4 * heads * mb) + up(48 * heads) + up(8 * heads * mb)
+                + 2 * up(16 * heads * mb) + up(64 * heads))
+        assert n.value == want, (heads, mb)
+        runs = -(-mb // 256)
+        assert 8 * heads * w <= 8 * heads * mb
+        assert runs == 1 or up(8 * heads * w) + 48 * heads * runs <= 8 * heads * mb
