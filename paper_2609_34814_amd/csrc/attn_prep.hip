@@ -14,6 +14,22 @@ namespace {
 // blocks 836, 850, 845 and 881, 8 x 208 rows (d 64) 195, 187, 186 and 182 us.
 constexpr int kSplitNum = 5, kSplitDen = 4;
 
+// Whether splitting pays. Whole, the launch takes about 9/10 of its longest row; split, each workgroup's share of the
+// kept blocks, on average half a chunk more at the end, and the chunks' cost: writing and merging partial tiles takes as long
+// as 16 kept blocks a chunk (24 for the smallest tiles, whose blocks are the shortest next to the fixed part). So rows are
+// split if
+//   0.9 longest > kept / slots + L / 2 + m chunks / slots + k,   m = 16 or 24, k = 4 (block 64) or 0.
+// Over 5,994 launches (14 to 400 blocks a head, 3% to 20 times as many rows as workgroups, equal and log-normal row
+// lengths, the four kernels) splitting whenever a row exceeded L was more than 3% slower than not splitting in 11%, up to
+// 2.8 times (equal rows, about half as many as workgroups: 768 rows of 24 of 64-token blocks, d 64, 77 us for 44); by
+// this rule in 0.4%, at most 1.12 times, and the geometric mean gain over not splitting is 1.614 for 1.589.
+struct SplitCost {
+  int merge, fixed;
+};
+__device__ __forceinline__ SplitCost split_cost(int d, int block) {
+  return {d == 64 && block == 64 ? 24 : 16, block == 64 ? 4 : 0};
+}
+
 // ---------------------------------------------------------------------------------------------
 // Preparation: everything a call needs before the attention kernel, in one launch, so that the latency
 // of the order tables (a few workgroups) hides behind the copy of V. Workgroups [0, n_xcd) build
@@ -34,6 +50,17 @@ __device__ __forceinline__ int wg_scan(int v, int32_t* part, int* all) {
   *all = __builtin_amdgcn_readlane(incl, PW - 1);
   __syncthreads();  // the partials are read before the next scan writes them
   return v + before;
+}
+
+// Maximum of nonnegative values over the workgroup's threads. One barrier pair.
+__device__ __forceinline__ int wg_max(int v, int32_t* part) {
+  for (int o = 1; o < 64; o <<= 1) v = max(v, __shfl_xor(v, o));
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
+  __syncthreads();
+  v = 0;
+  for (int w = 0; w < PW; ++w) v = max(v, part[w]);
+  __syncthreads();
+  return v;
 }
 
 // Late entries up to this many are placed by counting (four wavefronts: 1.3 us at 256, where the bitonic stages
@@ -296,24 +323,34 @@ __device__ void split_plan(const WaAttnLaunch& a, OrderLds& S, int slots) {
     }
     return false;
   };
+  const SplitCost cost = split_cost(a.head_dim, a.block);
+  auto pays = [&](int longest, int chunks) {
+    return (int64_t)slots * (9ll * longest - 5ll * L - 10 * cost.fixed) > 10 * ((int64_t)all + (int64_t)cost.merge * chunks);
+  };
   int mine = 0, total = 0;
   for (;;) {
     total = 0;
-    if (L >= a.mb) break;
-    int by_row = 0, h, r;
+    if (L >= a.mb || (!a.row_ptr && !pays(a.mb, 0))) break;  // (a caller's lists may name blocks repeatedly)
+    int by_row = 0, longest = 0, h, r;
     mine = 0;
     for (int i = t; i < rows; i += PT) {
-      const int n = slot_blocks(i, &h, &r);
+      int n = slot_blocks(i, &h, &r);
       if (n > L && queued(i, h)) mine += (n + L - 1) / L;
       if (a.perm) {
-        const int m = blocks(h, i - h * a.mb);
-        if (m > L) by_row += (m + L - 1) / L;
+        n = blocks(h, i - h * a.mb);
+        if (n > L) by_row += (n + L - 1) / L;
       }
+      longest = max(longest, n);
     }
     int row_total;
     wg_scan(by_row, S.part, &row_total);
     mine = wg_scan(mine, S.part, &total) - mine;  // chunks of the threads before this one
-    if (max(total, row_total) <= a.split_cap) break;
+    const bool fits = max(total, row_total) <= a.split_cap;
+    if (!pays(wg_max(longest, S.part), fits ? max(total, row_total) : 0)) {
+      total = 0;
+      break;
+    }
+    if (fits) break;
     L += (L + 1) / 2;
   }
   if (t < wa::kSplitShards) a.split[wa::split_counter(t)] = 0;

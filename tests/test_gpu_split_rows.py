@@ -12,6 +12,40 @@ from tests.gpu_util import bf16_dev, compare_blocks, dev_f64, u8_dev   # noqa: E
 from workloads.gen import custom, make_qkv   # noqa: E402
 
 MIN_L = 12   # the shortest L: on launches this small, rows of more kept blocks are split
+WGS = {(64, 64): 6, (64, 128): 2, (128, 64): 4, (128, 128): 2}   # workgroups on a compute unit
+
+
+def _plan(counts, d, block):
+    """(chunks, L, first L) of the split rule for the rows' kept blocks [heads][mb]."""
+    n, mb = np.asarray(counts).ravel(), np.asarray(counts).shape[-1]
+    slots = torch.cuda.get_device_properties(0).multi_processor_count * WGS[d, block]
+    cap = min((32 << 20) // (4 * block * (d + 2)), n.size * -(-mb // MIN_L))
+    kept = int(n.sum())
+    L = first = max(MIN_L, -(-(kept * 5 // 4) // slots))
+    while L < mb:
+        chunks = int((-(-n[n > L] // L)).sum())
+        use = chunks if chunks <= cap else 0
+        merge, fixed = (24 if d == 64 else 16, 4) if block == 64 else (16, 0)
+        if slots * (9 * int(n.max()) - 5 * L - 10 * fixed) <= 10 * (kept + merge * use):
+            break
+        if chunks <= cap:
+            return chunks, L, first
+        L += (L + 1) // 2
+    return 0, L, first
+
+
+def _planned(q, k, v, mask, block):
+    """(O, LSE, chunks, L): a call in a workspace of its own, from which the plan is read back."""
+    import ctypes
+    import paper_2609_34814_amd as W
+    from paper_2609_34814_amd import _lib as L
+    b, h, n, d = q.shape
+    shape, size = W.shape_of(b, h, n, d, block), ctypes.c_size_t(0)
+    assert L.load().wa_attn_workspace_size(ctypes.byref(shape), ctypes.byref(size)) == 0
+    ws = torch.zeros(W.attn_workspace_size(shape), dtype=torch.uint8, device="cuda")
+    o, lse = W.sparse_attn(q, k, v, mask, block=block, return_lse=True, workspace=ws)
+    chunks, longest = ws[size.value:size.value + 8].view(torch.int32).tolist()
+    return o, lse, chunks, longest
 
 
 def _mask(heads, mb, rng):
@@ -289,3 +323,36 @@ def test_workspace_without_room_for_split_rows(n_xcd, heads, mb):
         run(block=block, n_xcd=n_xcd, out=out, workspace=buf[:size.value])
         assert bool((buf[size.value:] == 0x5A).all())
         assert float((out.float() - want.float()).norm() / want.float().norm()) <= 2e-4
+
+
+def _rows_of(counts, rng):
+    """Mask with the given numbers of kept blocks [heads][mb], at random."""
+    heads, mb = counts.shape
+    m = np.zeros((1, heads, mb, mb), dtype=np.uint8)
+    for h in range(heads):
+        for i in range(mb):
+            m[0, h, i, rng.permutation(mb)[:counts[h, i]]] = 1
+    return m
+
+
+@pytest.mark.parametrize("d,block,heads,mb,most,few,long,splits", [
+    (64, 64, 12, 64, 24, 0, 0, False),      # equal rows, half as many as workgroups: chunks cost more than they save
+    (64, 64, 15, 66, 40, 0, 0, False),
+    (64, 128, 5, 48, 24, 0, 0, False),
+    (128, 128, 5, 48, 40, 0, 0, False),
+    (128, 64, 2, 64, 50, 0, 0, True),       # equal rows, few of them
+    (64, 128, 2, 48, 40, 0, 0, True),
+    (64, 64, 20, 80, 6, 3, 80, True),       # a few long rows
+    (128, 128, 12, 100, 8, 4, 100, True),
+])
+def test_rows_are_split_where_it_pays(d, block, heads, mb, most, few, long, splits):
+    """The plan of a call equals the rule, which weighs the longest row against the chunks' cost."""
+    rng = np.random.default_rng(mb)
+    counts = np.full((heads, mb), most)
+    counts.ravel()[rng.permutation(counts.size)[:few]] = long
+    chunks, longest, _ = _plan(counts, d, block)
+    assert (chunks > 0) == splits
+    g = torch.Generator(device="cuda").manual_seed(mb)
+    q, k, v = (torch.randn(1, heads, mb * block, d, generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    _, _, got, got_l = _planned(q, k, v, u8_dev(_rows_of(counts, rng)), block)
+    assert got == chunks and (not splits or got_l == longest)
