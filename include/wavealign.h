@@ -267,12 +267,11 @@ enum { WA_ATTN_BAD_PERM = 1, WA_ATTN_BAD_KV_INDEX = 2 };
  *                block count times the queue's share of workgroups exceeds the blocks
  *                queued after it) is taken first, longest first; the others keep their
  *                order. The order changes when rows run, never what they compute.
- *                In a launch of few rows whose workspace has the room (wa_attn_split_workspace_size),
  *                In a launch of few rows whose workspace has the room (wa_attn_split_workspace_size)
  *                and whose longest row would outlast the others, a row of more than L kept blocks is
  *                computed in chunks of at most L by several workgroups and merged in chunk order. Whether and
  *                at which L follows from the whole launch's lists and the device, so O is the same for
- *                every order, but a head's O may differ in its last bit from that of a launch with other
+ *                every order, but a head's O may differ by a bf16 rounding from that of a launch with other
  *                heads or batch entries (the order of float32 sums; probabilities are the same).
  *   o            out bf16 [B][H][N][d]
  *   lse          out float [B][H][N] natural-log sum-exp of the scaled scores, nullable
