@@ -336,8 +336,8 @@ wa_status wa_sparse_attn_vt(const void* q, const void* k, const void* vt, const 
  * wa_sparse_attn_vt, with the scheduler state (queue counters, prefix tables, the
  * orders of the last heads and the head-interleaved table) kept in a static device
  * array of the library instead of a workspace: WA_NOALLOC_SCRATCH_BYTES per GPU (and
- * 32.25 MiB for the state of split rows), taken when the library's code is loaded on
- * that GPU and held until the process ends. The call allocates and frees nothing. A shape whose state needs more
+ * 32.25 MiB for the state of split rows), taken when the runtime loads it, at the first such call on
+ * that GPU (which may be a captured one), and held until the process ends. The call allocates and frees nothing. A shape whose state needs more
  * (64 + n_xcd*(B*H+1) rounded up to 64, + n_xcd*T*M_B rounded up to 64, + 64 + B*H*M_B
  * int32, T as for wa_attn_workspace_size) is rejected with WA_ERR_WORKSPACE before
  * anything is enqueued. Every call on one GPU uses that GPU's one array and rebuilds

@@ -21,6 +21,7 @@ ARCH = "gfx950"
 SOURCES = {
     "attn_fwd.hip": [],
     "attn_prep.hip": [],
+    "attn_scratch.hip": [],
     "mask_kernels.hip": [],
     # the permutation must round exactly as specified: no fused multiply-add
     "perm_kernel.hip": ["-ffp-contract=off"],

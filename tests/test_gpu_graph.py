@@ -106,3 +106,45 @@ def test_path_graph_replays_match_eager(name):
         got = snapshot(lse_g)
         for key, want in ref.items():
             assert torch.equal(got[key], want), (name, rep, key)
+
+
+_NOALLOC_IN_A_NEW_PROCESS = """
+import torch, paper_2609_34814_amd as W
+free = lambda: torch.cuda.mem_get_info()[0]
+n, d, block = 20 * 64, 64, 64
+g = torch.Generator(device="cuda").manual_seed(1)
+q, k, v = (torch.randn(1, 2, n, d, generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+mask = torch.ones(1, 2, 20, 20, dtype=torch.uint8, device="cuda")
+rp, ci = W.compact_mask(mask, seq_len=n, block=block)
+vt = W.transpose_v(v, block=block)
+want = W.sparse_attn_vt(q, k, vt, rp, ci, block=block)
+out = torch.empty_like(want)
+torch.cuda.synchronize()
+torch.cuda.empty_cache()
+before = free()
+graph = torch.cuda.CUDAGraph()
+with torch.cuda.graph(graph):
+    W.sparse_attn_vt_noalloc(q, k, vt, rp, ci, block=block, out=out)
+torch.cuda.synchronize()
+held = (before - free()) / 2 ** 20
+for _ in range(3):
+    out.fill_(float("nan"))
+    torch.cuda.synchronize()
+    graph.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int16), want.view(torch.int16))
+print("held", held)
+"""
+
+
+def test_static_scratch_is_taken_at_the_first_call_that_needs_it():
+    """The arrays of the call that allocates nothing (36.25 MiB) are not held by a process that has only made the other
+    calls, and its first call may be a captured one."""
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", _NOALLOC_IN_A_NEW_PROCESS], cwd=root, capture_output=True, text=True,
+                       timeout=100)
+    assert r.returncode == 0, r.stderr[-2000:]
+    assert float(r.stdout.split("held")[1]) >= 36, r.stdout
