@@ -17,7 +17,7 @@ WGS = {(64, 64): 6, (64, 128): 2, (128, 64): 4, (128, 128): 2}   # workgroups on
 
 def _plan(counts, d, block):
     """(chunks, L, first L) of the split rule for the rows' kept blocks [heads][mb]."""
-    n, mb = np.asarray(counts).ravel(), np.asarray(counts).shape[-1]
+    n, mb = np.asarray(counts).ravel().astype(np.int64), np.asarray(counts).shape[-1]
     slots = torch.cuda.get_device_properties(0).multi_processor_count * WGS[d, block]
     cap = min((32 << 20) // (4 * block * (d + 2)), n.size * -(-mb // MIN_L))
     kept = int(n.sum())
@@ -80,7 +80,8 @@ def test_split_rows_vs_oracle(d, block, scale_k):
     kd = kd.to(torch.bfloat16)
     k_bits = kd.view(torch.int16).cpu().numpy().view(np.uint16)
     qd, vd, md = bf16_dev(q), bf16_dev(v), u8_dev(mask)
-    o, lse = W.sparse_attn(qd, kd, vd, md, block=block, return_lse=True)
+    o, lse, chunks, longest = _planned(qd, kd, vd, md, block)
+    assert (chunks, longest) == _plan(mask[0].sum(-1), d, block)[:2] == (heads * 11, MIN_L)   # 2 + 2 + 3 + 4 a head
     ref_o, ref_lse = A.block_sparse_attention(q, k_bits, v, mask, block)
     ref = {}
     for h in range(heads):
@@ -121,39 +122,58 @@ def test_split_rows_vs_oracle(d, block, scale_k):
     assert torch.equal(o.view(torch.int16), out.view(torch.int16))
 
 
-def test_split_rows_up_to_the_tile_limit():
-    """More chunks than tiles: L grows until the chunks fit; 300 rows of 64 full blocks (d 128)."""
-    import paper_2609_34814_amd as W
-    mb, heads, d, block = 64, 5, 128, 128
-    wl = custom("split-limit", heads=heads, head_dim=d, block=block, grid=(1, 1, mb * block), seed=22)
-    mask = np.ones((1, heads, mb, mb), dtype=np.uint8)
-    q, k, v = make_qkv(wl)
-    o, lse = W.sparse_attn(bf16_dev(q), bf16_dev(k), bf16_dev(v), u8_dev(mask), block=block, return_lse=True)
-    picks = [(0, h, i) for h in range(heads) for i in (0, 17, mb - 1)]
-    ref = A.block_sparse_attention_rows(q, k, v, mask, block, picks)
-    st = compare_blocks(dev_f64(o), ref, block, wl.seq_len, lse.cpu().numpy().astype(np.float64))
-    assert st["max_abs"] <= 1e-2 and st["rel_rms"] <= 1e-2 and st["lse"] <= 1e-3, st
-
-
-@pytest.mark.parametrize("d,block,heads,mb,n", [(64, 64, 10, 100, 30), (128, 128, 8, 48, 20)])
-def test_more_chunks_than_workgroups(d, block, heads, mb, n):
-    """Rows of n blocks each, all in two chunks, and more chunks than the device holds workgroups: the chunks past
-    the first of each workgroup come from the shards' counters, every queue entry is a split row but one a head."""
-    import paper_2609_34814_amd as W
-    wl = custom("split-many", heads=heads, head_dim=d, block=block, grid=(1, 1, mb * block), seed=23)
-    rng = np.random.default_rng(n)
-    mask = np.zeros((1, heads, mb, mb), dtype=np.uint8)
+def _rows_of(counts, rng):
+    """Mask with the given numbers of kept blocks [heads][mb], at random."""
+    heads, mb = counts.shape
+    m = np.zeros((1, heads, mb, mb), dtype=np.uint8)
     for h in range(heads):
         for i in range(mb):
-            mask[0, h, i, rng.permutation(mb)[: n if i else 1]] = 1
+            m[0, h, i, rng.permutation(mb)[:counts[h, i]]] = 1
+    return m
+
+
+def _against_oracle(wl, mask, picks, block, plan):
+    """A call whose chunks and L are those of `plan`, compared on the picked rows."""
     q, k, v = make_qkv(wl)
-    o, lse = W.sparse_attn(bf16_dev(q), bf16_dev(k), bf16_dev(v), u8_dev(mask), block=block, return_lse=True)
+    o, lse, chunks, longest = _planned(bf16_dev(q), bf16_dev(k), bf16_dev(v), u8_dev(mask), block)
+    assert (chunks, longest) == plan
     assert bool(torch.isfinite(o.float()).all()) and bool(torch.isfinite(lse).all())
-    picks = [(0, h, i) for h in range(heads) for i in (0, 1, h + 5, mb - 1)]
     ref = A.block_sparse_attention_rows(q, k, v, mask, block, picks)
     st = compare_blocks(dev_f64(o), ref, block, wl.seq_len, lse.cpu().numpy().astype(np.float64))
     assert st["max_abs"] <= 4 * 2.0 ** -9 * float(np.abs(A.bf16_to_f64(v)).max()), st
     assert st["rel_rms"] <= 1e-2 and st["lse"] <= 1e-3, st
+
+
+def test_split_rows_up_to_the_tile_limit():
+    """More chunks than tiles (d 128, block 128: 504): L grows until they fit, with 186 rows in two chunks."""
+    mb, heads, d, block = 128, 2, 128, 128
+    wl = custom("split-limit", heads=heads, head_dim=d, block=block, grid=(1, 1, mb * block), seed=22)
+    rng = np.random.default_rng(22)
+    counts = np.ones(heads * mb, dtype=np.int64)
+    rows = rng.permutation(heads * mb)[:186]
+    counts[rows[:180]], counts[rows[180:]] = 100, mb
+    counts = counts.reshape(heads, mb)
+    chunks, longest, first = _plan(counts, d, block)
+    limit = (32 << 20) // (4 * block * (d + 2))
+    assert int((-(-counts[counts > first] // first)).sum()) > limit >= chunks > 0 and longest > first
+    picks = [(0, int(r) // mb, int(r) % mb) for r in rows[[0, 1, 90, 179, 180, 185]]]
+    _against_oracle(wl, _rows_of(counts, rng), picks, block, (chunks, longest))
+
+
+@pytest.mark.parametrize("d,block,heads", [(64, 64, 8), (64, 128, 3)])
+def test_more_chunks_than_workgroups(d, block, heads):
+    """Rows of 30 blocks in two chunks each, a few full rows and one row of one block a head: more chunks than the device
+    holds workgroups (the shapes whose tile limit allows it), so the chunks past the first of each workgroup come
+    from the shards' counters."""
+    mb = 100
+    wl = custom("split-many", heads=heads, head_dim=d, block=block, grid=(1, 1, mb * block), seed=23)
+    rng = np.random.default_rng(d + block)
+    counts = np.full((heads, mb), 30)
+    counts[:, 0], counts[:, mb - 1], counts[0, 7], counts[1, 9] = 1, mb, mb, mb
+    chunks, longest, _ = _plan(counts, d, block)
+    assert chunks > torch.cuda.get_device_properties(0).multi_processor_count * WGS[d, block] and longest < 30
+    picks = [(0, h, i) for h in range(heads) for i in (0, 1, h + 5, mb - 1)] + [(0, 0, 7), (0, 1, 9)]
+    _against_oracle(wl, _rows_of(counts, rng), picks, block, (chunks, longest))
 
 
 @pytest.mark.parametrize("d,block", [(64, 64), (64, 128), (128, 64), (128, 128)])
@@ -323,16 +343,6 @@ def test_workspace_without_room_for_split_rows(n_xcd, heads, mb):
         run(block=block, n_xcd=n_xcd, out=out, workspace=buf[:size.value])
         assert bool((buf[size.value:] == 0x5A).all())
         assert float((out.float() - want.float()).norm() / want.float().norm()) <= 2e-4
-
-
-def _rows_of(counts, rng):
-    """Mask with the given numbers of kept blocks [heads][mb], at random."""
-    heads, mb = counts.shape
-    m = np.zeros((1, heads, mb, mb), dtype=np.uint8)
-    for h in range(heads):
-        for i in range(mb):
-            m[0, h, i, rng.permutation(mb)[:counts[h, i]]] = 1
-    return m
 
 
 @pytest.mark.parametrize("d,block,heads,mb,most,few,long,splits", [
