@@ -95,26 +95,11 @@ __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast
 // gives each lane half 8 consecutive tile rows.
 __device__ __forceinline__ int perm16(int r) { return ((r >> 2) & 1) * 8 + ((r >> 3) & 1) * 4 + (r & 3); }
 
-// Tiles have rows of RB bytes (256 or 128) in 16-byte chunks. Physical chunk of (row, chunk):
-// K tiles are read one row per lane (ds_read_b128), 16 rows per wavefront quarter;
-// V tiles are read by the transposing loads, four consecutive rows at a time.
+// Tiles have rows of RB bytes (256 or 128) in 16-byte chunks. Physical chunk of (row, chunk): both tiles are read
+// one row per lane (ds_read_b128), 16 rows per wavefront quarter.
 template <int RB>
-__device__ __forceinline__ int swz_k(int row, int chunk) {
-  return RB == 256 ? (chunk ^ (row & 15)) : (chunk ^ ((row >> 1) & 7));
-}
-template <int RB>
-__device__ __forceinline__ int swz_v(int row, int chunk) {
-  const int e = row & 3;  // XOR 0, 6, 12, 10 (256-byte rows) or 0, 2, 4, 6 (128-byte rows): stays in the row
-  return RB == 256 ? (chunk ^ ((e << 1) ^ (e << 2))) : (chunk ^ (e << 1));
-}
-template <int RB, bool V>
 __device__ __forceinline__ int swz(int row, int chunk) {
-  return V ? swz_v<RB>(row, chunk) : swz_k<RB>(row, chunk);
-}
-
-template <int RB>
-__device__ __forceinline__ uint4 lds_chunk(const unsigned char* tile, int row, int chunk) {
-  return *(const uint4*)(tile + row * RB + swz_k<RB>(row, chunk) * 16);
+  return RB == 256 ? (chunk ^ (row & 15)) : (chunk ^ ((row >> 1) & 7));
 }
 
 template <int D, int BLK>
@@ -159,30 +144,30 @@ __device__ __forceinline__ void store_through(float* p, float x, float y, float 
 // DMA geometry of a tile with rows of RB bytes copied by NW wavefronts: instruction i of wavefront w
 // writes tile rows [(i*NW + w)*RPI, +RPI), lane l the chunk (l mod LPR) of row (l / LPR) among them.
 // The global source of that slot is chunk swz(row, slot) of the row (each swizzle is an involution).
-template <int RB, int NW, bool V>
+template <int RB, int NW>
 struct Dma {
   static constexpr int RPI = 1024 / RB;   // rows per instruction
   static constexpr int LPR = RB / 16;     // lanes per row
   // the swizzle of a lane's slot is the same for every instruction when the row step is a multiple of
   // the swizzle's row period
-  static constexpr bool kInvariant = (NW * RPI) % (V ? 4 : 16) == 0;
+  static constexpr bool kInvariant = (NW * RPI) % 16 == 0;
   __device__ static __forceinline__ int row(int i, int w, int lane) { return (i * NW + w) * RPI + lane / LPR; }
   // per-lane source bytes relative to tile row (i*NW)*RPI, for source rows `stride` bytes apart
   __device__ static __forceinline__ uint32_t lane_bytes(int i, int w, int lane, uint32_t stride = RB) {
     const int r0 = w * RPI + lane / LPR;
     const int rs = kInvariant ? r0 : row(i, w, lane);
-    return (uint32_t)r0 * stride + (uint32_t)(swz<RB, V>(rs, lane % LPR) * 16);
+    return (uint32_t)r0 * stride + (uint32_t)(swz<RB>(rs, lane % LPR) * 16);
   }
 };
 
-// DMA of rows [key0, key0 + BLK) of a K or V head (g: its first row) into a swizzled tile. In the
+// DMA of rows [key0, key0 + BLK) of a K head (g: its first row) into a swizzled tile. In the
 // ragged last block, rows past the end of the sequence are clamped to the last row (their scores
 // are masked, so their probabilities are 0).
-template <int D, int BLK, bool V>
+template <int D, int BLK>
 __device__ __forceinline__ void issue_tile(unsigned char* tile, const unsigned char* g, int key0, int n, int w,
                                            int lane) {
   using C = Cfg<D, BLK>;
-  using G = Dma<C::RB, C::NW, V>;
+  using G = Dma<C::RB, C::NW>;
   if (key0 + BLK <= n) {
 #pragma unroll
     for (int i = 0; i < C::NK; ++i)
@@ -193,7 +178,7 @@ __device__ __forceinline__ void issue_tile(unsigned char* tile, const unsigned c
     for (int i = 0; i < C::NK; ++i) {
       const int r = G::row(i, w, lane);
       const uint32_t off = (uint32_t)min(key0 + r, n - 1) * (uint32_t)C::RB +
-                           (uint32_t)(swz<C::RB, V>(r, lane % G::LPR) * 16);
+                           (uint32_t)(swz<C::RB>(r, lane % G::LPR) * 16);
       dma16(g, off, tile + (i * C::NW + w) * 1024);
     }
   }
@@ -205,7 +190,7 @@ template <int D, int BLK>
 __device__ __forceinline__ void issue_vt(unsigned char* tile, const unsigned char* vtg, uint32_t row_bytes, int key0,
                                          int w, int lane) {
   using C = Cfg<D, BLK>;
-  using G = Dma<C::VRB, C::NW, false>;
+  using G = Dma<C::VRB, C::NW>;
 #pragma unroll
   for (int i = 0; i < C::NK; ++i)
     dma16(vtg + (int64_t)key0 * 2 + (int64_t)(i * C::NW * G::RPI) * row_bytes, G::lane_bytes(i, w, lane, row_bytes),
@@ -371,7 +356,7 @@ __global__ __launch_bounds__(BLK * 2, D == 64 && BLK == 64 ? 3 : 2) void attn_fw
   {
     const int kr = 16 * ((lane & 31) >> 4) + perm16(lane & 15);
 #pragma unroll
-    for (int s = 0; s < C::KS; ++s) kofs[s] = (uint32_t)(kr * C::RB + swz_k<C::RB>(kr, 2 * s + hf) * 16);
+    for (int s = 0; s < C::KS; ++s) kofs[s] = (uint32_t)(kr * C::RB + swz<C::RB>(kr, 2 * s + hf) * 16);
   }
   // the same for the V^T operand of k-step ks (16 keys; d tile dt adds dt 32 VRB)
   uint32_t vofs[2 * C::KT];
@@ -379,7 +364,7 @@ __global__ __launch_bounds__(BLK * 2, D == 64 && BLK == 64 ? 3 : 2) void attn_fw
     const int kr = 16 * ((lane & 31) >> 4) + perm16(lane & 15);
 #pragma unroll
     for (int ks = 0; ks < 2 * C::KT; ++ks)
-      vofs[ks] = (uint32_t)(kr * C::VRB + swz_k<C::VRB>(kr, 2 * ks + hf) * 16);
+      vofs[ks] = (uint32_t)(kr * C::VRB + swz<C::VRB>(kr, 2 * ks + hf) * 16);
   }
 
   for (bool first = true;; first = false) {
@@ -511,7 +496,7 @@ __global__ __launch_bounds__(BLK * 2, D == 64 && BLK == 64 ? 3 : 2) void attn_fw
       scores(sacc);
       // every wavefront is done with K_j: start K_{j+1}
       WA_BARRIER();
-      if (has_next) issue_tile<D, BLK, false>(k_lds, kg, j_next * BLK, n, w, lane_o);
+      if (has_next) issue_tile<D, BLK>(k_lds, kg, j_next * BLK, n, w, lane_o);
 
       // ---- softmax numerators (log2 domain) ----
       if constexpr (MASKED) mask_tail(sacc, n - j_cur * BLK, lane_o);
@@ -584,7 +569,7 @@ __global__ __launch_bounds__(BLK * 2, D == 64 && BLK == 64 ? 3 : 2) void attn_fw
             j_cur = 0;
             bad_kv = 1;
           }
-          issue_tile<D, BLK, false>(k_lds, kg, j_cur * BLK, n, w, lane);
+          issue_tile<D, BLK>(k_lds, kg, j_cur * BLK, n, w, lane);
           issue_vt<D, BLK>(v_lds, vtg, vt_row_bytes, j_cur * BLK, w, lane);
         }
         // the Q loads (issued first) are complete; the first tiles stay in flight
@@ -624,7 +609,7 @@ __global__ __launch_bounds__(BLK * 2, D == 64 && BLK == 64 ? 3 : 2) void attn_fw
       for (int e2 = m0; e2 < m1; ++e2) {
         int j = cols[e2];
         if ((unsigned)j >= (unsigned)mb) j = 0;
-        issue_tile<D, BLK, false>(k_lds, kg, j * BLK, n, w, lane);
+        issue_tile<D, BLK>(k_lds, kg, j * BLK, n, w, lane);
         WA_WAIT_VM(0);
         WA_BARRIER();
         f32x16 sacc[C::KT];
