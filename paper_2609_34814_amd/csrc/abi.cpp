@@ -212,6 +212,15 @@ wa_status launch_attn(const void* q, const void* k, const void* v, const void* v
   return WA_OK;
 }
 
+wa_status compute_units(int* cus) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
+  e = hipDeviceGetAttribute(cus, hipDeviceAttributeMultiprocessorCount, dev);
+  if (e != hipSuccess) return hip_fail(e, "hipDeviceGetAttribute");
+  return WA_OK;
+}
+
 wa_status perm_launch_common(const uint8_t* mask, const Dims& d, const PermWs& L, char* base, hipStream_t st,
                              int32_t* row_nnz_out) {
   int32_t* row_nnz = row_nnz_out ? row_nnz_out : (int32_t*)(base + L.row_nnz);
@@ -252,11 +261,9 @@ wa_status wa_wave_size(int32_t head_dim, int32_t block, int32_t* wave_per_xcd) {
   if (!wave_per_xcd) return fail(WA_ERR_INVALID_ARG, "wave_per_xcd is null");
   if ((head_dim != 64 && head_dim != 128) || (block != 64 && block != 128))
     return fail(WA_ERR_UNSUPPORTED, "head_dim %d / block %d not supported", head_dim, block);
-  int dev = 0, cus = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
-  e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  if (e != hipSuccess) return hip_fail(e, "hipDeviceGetAttribute");
+  int cus = 0;
+  const wa_status s = compute_units(&cus);
+  if (s != WA_OK) return s;
   // 8 XCDs share the compute units evenly on MI355X (256 CUs = 8 x 32)
   const int per_xcd = cus >= 8 ? cus / 8 : cus;
   *wave_per_xcd = per_xcd * wa::wave_wgs(head_dim, block);
@@ -323,6 +330,9 @@ wa_status wa_build_permutation(const uint8_t* mask, const wa_shape* shape, const
     s = wa_wave_size(d.d, d.blk, &wave);
     if (s != WA_OK) return s;
   }
+  int cus = 0;
+  s = compute_units(&cus);
+  if (s != WA_OK) return s;
   hipStream_t st = (hipStream_t)stream;
   char* base = (char*)workspace;
   s = perm_launch_common(mask, d, L, base, st, nullptr);
@@ -334,7 +344,7 @@ wa_status wa_build_permutation(const uint8_t* mask, const wa_shape* shape, const
   a.head_stats = nullptr;
   a.perm = perm; a.flags = head_flags; a.embedding = embedding; a.stage1 = stage1_order; a.seg_start = seg_start;
   a.bh = (int32_t)d.bh; a.m = d.mb; a.n = d.mb;
-  a.wave = wave; a.n_xcd = params->n_xcd; a.iters = params->iters; a.skip_mode = params->skip_mode;
+  a.cus = cus; a.wave = wave; a.n_xcd = params->n_xcd; a.iters = params->iters; a.skip_mode = params->skip_mode;
   a.stats_only = 0; a.block = d.blk; a.head_dim = d.d; a.seed = params->seed;
   a.prof = params->profile ? *params->profile : kDefaultProfile;
   hipError_t e = wa_launch_perm(a, st);

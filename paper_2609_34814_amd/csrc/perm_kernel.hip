@@ -1343,9 +1343,11 @@ hipError_t wa_launch_perm(const WaPermLaunch& launch, hipStream_t stream) {
     hipLaunchKernelGGL(perm_skip_state_kernel, dim3(a.bh), dim3(64), 0, stream, a, runs);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   } else {
-    // one workgroup a compute unit (256), at least one tile a wavefront (so at most one slice a statistics run)
+    // at most one workgroup a compute unit, at least one tile a wavefront (so at most one slice a statistics run). From
+    // more than half as many heads as compute units on that is one slice: 130 heads of 1,100 blocks take 408 us a
+    // call, 128 heads 334 (683 and 680 with a workgroup per 128 lines)
     const int most = ((lines + 15) / 16 + NWAVE - 1) / NWAVE;
-    a.slices = std::max(1, std::min(most, 256 / a.bh));
+    a.slices = std::max(1, std::min(most, a.cus / a.bh));
     const dim3 grid((unsigned)((int64_t)a.bh * a.slices)), block(SliceCfg::NT);
     for (int it = 0; it <= a.iters; ++it) {
       const int last = it == a.iters;

@@ -48,6 +48,7 @@ struct WaPermLaunch {
   int32_t* stage1;          // [bh][m], nullable
   int32_t* seg_start;       // [bh][n_xcd+1], nullable
   int32_t bh, m, n;
+  int32_t cus;     // compute units of the device
   int32_t slices;  // workgroups per head of the centred-product kernels (set by wa_launch_perm)
   int32_t wave, n_xcd, iters, skip_mode, stats_only;
   int32_t block, head_dim;
