@@ -272,7 +272,8 @@ enum { WA_ATTN_BAD_PERM = 1, WA_ATTN_BAD_KV_INDEX = 2 };
  *                computed in chunks of at most L by several workgroups and merged in chunk order. Whether and
  *                at which L follows from the whole launch's lists and the device, so O is the same for
  *                every order, but a head's O may differ by a bf16 rounding from that of a launch with other
- *                heads or batch entries (the order of float32 sums; probabilities are the same).
+ *                heads or batch entries (the order of float32 sums; probabilities are the same, except in a
+ *                row recomputed against an exact maximum, where each chunk takes its own blocks').
  *   o            out bf16 [B][H][N][d]
  *   lse          out float [B][H][N] natural-log sum-exp of the scaled scores, nullable
  *   status       out int32 status word (WA_ATTN_* bits), device, nullable
