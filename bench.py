@@ -119,7 +119,7 @@ PMC_PASSES = {
 def _read_bytes_e(c):
     """L2 read bytes to the fabric from pass E (128-, 64- and 32-byte requests), and the share of them
     addressed to DRAM: on MI355X those go through the 256 MiB last-level cache on the way, and no
-    counter of this pool tells its hits from HBM reads."""
+    counter that rocprofv3 lists tells its hits from HBM reads."""
     rd, r32, bub, dram = (c["TCC_EA0_RDREQ_sum"], c["TCC_EA0_RDREQ_32B_sum"], c["TCC_BUBBLE_sum"],
                           c["TCC_EA0_RDREQ_DRAM_sum"])
     total = bub * 128.0 + (rd - bub - r32) * 64.0 + r32 * 32.0
@@ -197,7 +197,7 @@ def summarize_pmc(root: str, workload: str, variants, warmup: int, steps: int, b
               "TCC_HIT / (TCC_HIT + TCC_MISS). fabric rd GB = FETCH_SIZE x copy factor: what the eight L2s read "
               "from the fabric, i.e. from the 256 MiB last-level cache and HBM together. DRAM rd GB = pass E's "
               "read bytes (128/64/32-byte requests) x copy factor x TCC_EA0_RDREQ_DRAM / TCC_EA0_RDREQ: the reads "
-              "addressed to DRAM, which still includes last-level-cache hits (this pool exposes no counter that "
+              "addressed to DRAM, which still includes last-level-cache hits (rocprofv3 lists no counter that "
               "separates them, so true HBM read bytes cannot be measured here). K/V xcd GB: compulsory K/V if each "
               "XCD fetches every block its own rows need once (per-XCD model, see bench.py). MFMA busy % = "
               "SQ_VALU_MFMA_BUSY_CYCLES / (1024 SIMDs x GRBM_GUI_ACTIVE / 8), against the clock the chip ran at "
